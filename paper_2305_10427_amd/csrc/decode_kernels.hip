@@ -242,6 +242,270 @@ __global__ __launch_bounds__(W * kWave) void k_attn_split(AttnArgs a) {
   }
 }
 
+// Attention of up to 16 consecutive rows of one sentence and head on the matrix
+// cores, for launches whose sentences have several rows (Jacobi blocks,
+// teacher-forced rows, encoder rows): one workgroup of four waves per
+// (sentence, 16-row tile, head).
+//
+// The arithmetic is chunk_eval's, element for element.  v_mfma_f32_16x16x4_f32
+// adds its four products one after another with a fused multiply-add each (bit
+// patterns compared with an fmaf chain over normal, subnormal, overflowing and
+// arbitrary operands), so an accumulator that takes dimensions j, j + 4, j + 8,
+// ... is the same chain as chunk_eval's acc4[j], and the sum over a group of 16
+// keys is the same balanced tree.  A row is therefore bitwise the same as from
+// k_attn / k_attn_split.
+//
+// Per 64-key chunk wave w scores keys 16 w .. 16 w + 15 (the products' rows)
+// for the 16 queries (their columns), so a lane holds four consecutive keys of
+// one query; then, p through LDS, the wave multiplies key half w / 2 with
+// dimension half w & 1 of V, a lane holding NT * 4 consecutive dimensions of
+// one query; waves 0 and 1 add the halves and keep the running state.
+//
+// k_attn at many rows is bound by vector issue: a wave spends about 450
+// instructions on one row's chunk and loads the chunk for that row alone.
+// Here 16 rows share the loads and the 32 matrix and about 400 vector
+// instructions of each of the four waves (large model, 512 rows in blocks of
+// 16: 14.9 -> 8.2 us per launch; 3840 encoder rows 111 -> 44 us); vector issue
+// is still the bound, and at few tiles the latency of the chunk's two barriers.
+//
+// Keys past a row's count have p = 0 (past the sentence's last key the loads
+// return zeros); where a later row of the block holds a non-finite V entry,
+// 0 * NaN must not reach the rows before it, so such chunks are multiplied
+// row by row with that row's keys only (s_bad; causal launches).
+__device__ __forceinline__ float row16_swap_max(float v) {   // over lanes n, n + 16, n + 32, n + 48
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
+}
+__device__ __forceinline__ float row16_swap_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+}
+
+// N elements of AT (as dwords) from a buffer, zeros past its end.
+template <int BYTES> struct BufWords;
+template <> struct BufWords<2> {
+  uint32_t w[1];
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    w[0] = __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0);
+  }
+};
+template <> struct BufWords<4> {
+  uint32_t w[1];
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+  }
+};
+template <> struct BufWords<8> {
+  uint32_t w[2];
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+    w[0] = v[0];
+    w[1] = v[1];
+  }
+};
+template <> struct BufWords<16> {
+  uint32_t w[4];
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = v[i];
+  }
+};
+template <typename AT> __device__ __forceinline__ float word_elt(const uint32_t* w, int e);
+template <> __device__ __forceinline__ float word_elt<float>(const uint32_t* w, int e) { return __uint_as_float(w[e]); }
+template <> __device__ __forceinline__ float word_elt<bf16_t>(const uint32_t* w, int e) {
+  return __uint_as_float((e & 1) ? w[e >> 1] & 0xffff0000u : w[e >> 1] << 16);
+}
+
+template <typename AT, int DH>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH > 64 ? 2 : 3))) void k_attn_tile(AttnArgs a) {
+  constexpr int NT = DH > 64 ? DH / 64 : 1;   // 16-dimension tiles of V per wave
+  constexpr int PV_WAVES = DH / (16 * NT);    // waves that multiply V (two for DH = 32, else all)
+  constexpr int KT = DH / 16;                 // 16-dimension steps of a score
+  constexpr int ES = sizeof(AT);
+  constexpr int PLD = kAttnChunk + 4;         // padded row of the weights p
+  __shared__ __align__(16) float s_p[16][PLD];
+  __shared__ __align__(16) float s_max[16][4], s_sum[16][4];
+  __shared__ int s_bad;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int n = lane & 15, g = lane >> 4;
+  const int hh = blockIdx.x, r_in = blockIdx.y * 16, s = blockIdx.z;
+  // the sentence's rows: first row, rows of this tile, position of its first
+  // row (loads on a straight path: unused ones read valid words of q)
+  const int* any = reinterpret_cast<const int*>(a.q);
+  const int klen_s = *(a.causal ? any : a.klen + s);
+  const bool dense = a.st == nullptr;
+  const SentState st = *(dense ? reinterpret_cast<const SentState*>(any) : a.st + s);
+  const int row0 = (dense ? s * a.rows.per_sent : st.row0) + r_in;
+  const int cnt = min(16, (dense ? a.rows.per_sent : st.L) - r_in);
+  const int pos0 = (dense ? 0 : st.i) + r_in;
+  const int nk_max = a.causal ? pos0 + cnt : klen_s;
+  if (cnt <= 0) return;                  // workgroup-uniform
+  const size_t base = (static_cast<size_t>(s) * a.H + hh) * a.T * DH;
+  const int bytes = nk_max * DH * ES;
+  const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<AT*>(static_cast<const AT*>(a.kc) + base), static_cast<short>(0), bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<AT*>(static_cast<const AT*>(a.vc) + base), static_cast<short>(0), bytes, 0x00020000);
+  // K: key 16 wave + n, dimensions 16 t + 4 g .. + 3; V: keys 16 t + 4 g + j, this lane's NT dimensions
+  const uint32_t ko = ((16 * wave + n) * DH + 4 * g) * ES;
+  const uint32_t vo = (4 * g * DH + 16 * NT * (wave % PV_WAVES) + NT * n) * ES;
+  BufWords<4 * ES> kw[KT];
+  BufWords<NT * ES> vw[4][4];
+  auto load_chunk = [&](int key0) __attribute__((always_inline)) {
+    // in the lane offset, which the range check covers
+    const uint32_t kc = ko + static_cast<uint32_t>(key0) * (DH * ES), vc = vo + static_cast<uint32_t>(key0) * (DH * ES);
+#pragma unroll
+    for (int t = 0; t < KT; ++t) kw[t].load(kr, kc + 16 * t * ES);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) vw[t][j].load(vr, vc + (16 * t + j) * (DH * ES));
+  };
+  // the queries: row n, dimensions 16 t + 4 g .. + 3
+  floatx4_t q[KT];
+  const float* qp = a.q + static_cast<size_t>(row0 + min(n, cnt - 1)) * a.ldq + hh * DH + 4 * g;
+#pragma unroll
+  for (int t = 0; t < KT; ++t) q[t] = *reinterpret_cast<const floatx4_t*>(qp + 16 * t);
+  load_chunk(0);
+  const int nk = n < cnt ? (a.causal ? pos0 + n + 1 : nk_max) : 0;   // keys of this lane's row
+  if (threadIdx.x == 0) s_bad = 0;
+  __syncthreads();
+  float m = -INFINITY, l = 0.f;
+  floatx4_t o[NT];
+#pragma unroll
+  for (int u = 0; u < NT; ++u) o[u] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+
+  for (int key0 = 0; key0 < nk_max; key0 += kAttnChunk) {
+    // scores of this wave's 16 keys: element i of a lane is key 16 wave + 4 g + i of row n
+    floatx4_t sc4[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sc4[j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < KT; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        sc4[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(word_elt<AT>(kw[t].w, j), q[t][j], sc4[j], 0, 0, 0);
+    const floatx4_t dot = (sc4[0] + sc4[1]) + (sc4[2] + sc4[3]);
+    BufWords<NT * ES> vc[4][4];            // this chunk's V entries; the next chunk's loads leave now
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) vc[t][j] = vw[t][j];
+    if (key0 + kAttnChunk < nk_max) load_chunk(key0 + kAttnChunk);
+    if (a.causal && key0 + kAttnChunk > pos0 + 1) {   // a chunk that some row sees in part
+      float z = 0.f;                       // stays 0 unless an entry is NaN or infinite
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int u = 0; u < NT; ++u) z = fmaf(word_elt<AT>(vc[t][j].w, u), 0.f, z);
+      if (z != 0.f) s_bad = 1;
+    }
+    const int key = key0 + 16 * wave + 4 * g;
+    float sc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sc[i] = key + i < nk ? dot[i] * a.scale : -INFINITY;
+    const float mx = row16_swap_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])));
+    if (g == 0) s_max[n][wave] = mx;
+    __syncthreads();
+    const floatx4_t m4 = *reinterpret_cast<const floatx4_t*>(s_max[n]);
+    const bool bad = __builtin_amdgcn_readfirstlane(s_bad) != 0;   // workgroup-uniform (set before this barrier only)
+    const float mc = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
+    floatx4_t p;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = key + i < nk ? expf(sc[i] - mc) : 0.f;
+    const float sm = row16_swap_sum((p[0] + p[1]) + (p[2] + p[3]));
+    *reinterpret_cast<floatx4_t*>(&s_p[n][16 * wave + 4 * g]) = p;
+    if (g == 0) s_sum[n][wave] = sm;
+    // the fold's factors (fold_chunk)
+    const float mn = fmaxf(m, mc);
+    const float a1 = expf(m - mn);
+    const float a2 = expf(mc - mn);
+    __syncthreads();
+    if (PV_WAVES == 4 || wave < PV_WAVES) {   // wave-uniform
+      const floatx4_t l4 = *reinterpret_cast<const floatx4_t*>(s_sum[n]);
+      floatx4_t pa[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) pa[t] = *reinterpret_cast<const floatx4_t*>(&s_p[n][16 * t + 4 * g]);
+      const float lc = (l4[0] + l4[1]) + (l4[2] + l4[3]);
+      // V^T . p, key halves apart: all rows at once, or row by row with that row's keys only
+      floatx4_t oc[NT];
+#pragma unroll
+      for (int u = 0; u < NT; ++u) oc[u] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int r = bad ? 0 : 15; r < 16; ++r) {
+        float vm[4][4][NT];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int u = 0; u < NT; ++u) vm[t][j][u] = word_elt<AT>(vc[t][j].w, u);
+        if (bad) {
+          const int nk_r = __builtin_amdgcn_readlane(nk, r);
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+              for (int u = 0; u < NT; ++u)
+                if (key0 + 16 * t + 4 * g + j >= nk_r) vm[t][j][u] = 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+          floatx4_t half[2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            floatx4_t acc[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 2 * h; t < 2 * h + 2; ++t)
+#pragma unroll
+              for (int j = 0; j < 4; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vm[t][j][u], pa[t][j], acc[j], 0, 0, 0);
+            half[h] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+          }
+          if (!bad || n == r) oc[u] = half[0] + half[1];
+        }
+      }
+      if (key0 < nk) {                     // the row has keys in this chunk
+#pragma unroll
+        for (int u = 0; u < NT; ++u) o[u] = o[u] * a1 + oc[u] * a2;
+        l = l * a1 + lc * a2;
+        m = mn;
+      }
+    }
+  }
+  if (wave < PV_WAVES && n < cnt) {
+    // element i of o[u] is dimension 16 NT wave + NT (4 g + i) + u: NT * 4 consecutive ones
+    float y[4 * NT];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int u = 0; u < NT; ++u) y[NT * i + u] = o[u][i] / l;
+    AT* out = static_cast<AT*>(a.out);
+    const int row = row0 + n;
+    const int k0 = hh * DH + 16 * NT * wave + NT * 4 * g;
+#pragma unroll
+    for (int e = 0; e < 4 * NT; e += 4) {
+      const size_t at = a.out_feed ? feed_index<Mma<AT>::KS, Mma<AT>::EPL>(row, k0 + e, a.H * DH)
+                                   : static_cast<size_t>(row) * a.ldo + k0 + e;
+      if constexpr (ES == 2)
+        *reinterpret_cast<uint2*>(out + at) = make_uint2(pack_bf16x2(y[e], y[e + 1]), pack_bf16x2(y[e + 2], y[e + 3]));
+      else
+        *reinterpret_cast<float4*>(out + at) = make_float4(y[e], y[e + 1], y[e + 2], y[e + 3]);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Token embedding x = E[tok] * scale + PE(pos), PE the interleaved sinusoid
 // (columns 2i, 2i+1 = sin, cos of pos * 10000^(-2i/d)), evaluated in double
@@ -934,9 +1198,42 @@ static hipError_t launch_attn_t(const AttnArgs& a, int grid, hipStream_t s) {
   return a.one_source ? launch_attn_f<AT, 1>(a, grid, s) : launch_attn_f<AT, 0>(a, grid, s);
 }
 
+template <typename AT>
+static hipError_t launch_attn_tile(const AttnArgs& a, hipStream_t s) {
+  const dim3 grid(a.H, (a.sent_rows + 15) / 16, a.n_sent);
+  switch (a.dh) {
+    case 32: hipLaunchKernelGGL((k_attn_tile<AT, 32>), grid, dim3(256), 0, s, a); break;
+    case 64: hipLaunchKernelGGL((k_attn_tile<AT, 64>), grid, dim3(256), 0, s, a); break;
+    case 128: hipLaunchKernelGGL((k_attn_tile<AT, 128>), grid, dim3(256), 0, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+// Measured (large model, 16 heads, blocks of 16; us per launch, one wave or two
+// per row against 16-row tiles): 512 rows 14.9 against 8.2, 256 rows 11.3 / 8.2,
+// 128 rows 8.8 / 7.9, 64 rows 6.4 / 7.4; 1032 teacher-forced rows 31.8 / 17.0;
+// 53 rows of 8 heads 3.4 / 4.4.  A tile of few rows wastes its products: with
+// blocks of 5 the two are equal.
+bool attn_tiled(int dh, int heads, int sent_rows, int R_max) {
+  return dh >= 32 && sent_rows >= 8 && R_max * heads >= 2048;
+}
+
 hipError_t launch_attn(int dtype, const AttnArgs& args, int R_max, hipStream_t s) {
   if (args.dh > kMaxHeadDim || args.T > kMaxKeys) return hipErrorInvalidValue;
   if (args.one_source && (args.causal || args.klen == nullptr)) return hipErrorInvalidValue;
+  if (!args.causal && args.klen == nullptr) return hipErrorInvalidValue;
+  if (R_max > 0 && attn_tiled(args.dh, args.H, args.sent_rows, R_max)) {
+    AttnArgs a = args;
+    const int per = a.rows.per_sent;
+    if (a.rows.sent == nullptr ? per < 1 || R_max % per != 0 : a.st == nullptr || a.n_sent < 1) return hipErrorInvalidValue;
+    if (a.rows.sent == nullptr) {        // dense rows: the launch bound is the row count
+      a.st = nullptr;
+      a.n_sent = R_max / per;
+      a.sent_rows = per;
+    }
+    return dtype == DT_BF16 ? launch_attn_tile<bf16_t>(a, s) : launch_attn_tile<float>(a, s);
+  }
   const int grid = (R_max + kAttnRows - 1) / kAttnRows * args.H;
   if (grid == 0) return hipSuccess;
   AttnArgs a = args;

@@ -139,6 +139,11 @@ struct AttnArgs {
   int max_keys;            // host bound on any row's key count (0: unknown); chooses the launch shape only
   int one_source;          // 1: every row is of sentence 0 and non-causal (a batch of one): key slots are
                            // loaded before klen[0] arrives (the caches must hold finite values throughout)
+  // 16-row tiles (attn_tiled): a host bound on the rows of one sentence (0: unknown), and for rows placed by a
+  // list the control step's sentence states (row0, L, i of the current rows) and their number
+  int sent_rows;
+  const struct SentState* st;
+  int n_sent;
 };
 
 struct EmbedArgs {
@@ -300,6 +305,9 @@ void gemm_tiled_init();
 hipError_t launch_gemm_tiled(int epi, int ksplit, const GemmArgs& a, hipStream_t s);
 int gemm_tiled_cfg(int epi, int N, int rows);
 hipError_t launch_gemm_tiled_cfg(int epi, int ksplit, int cfg, const GemmArgs& a, hipStream_t s);
+// Whether launch_attn evaluates 16 rows of a head together on the matrix cores
+// (bitwise the same rows): sentences of up to sent_rows rows, launch bound R_max.
+bool attn_tiled(int dh, int heads, int sent_rows, int R_max);
 hipError_t launch_attn(int dtype, const AttnArgs& a, int R_max, hipStream_t s);
 // Fused vocabulary projection + argmax for at most 16 rows (streaming kernel);
 // writes vocab_grid(dtype, V, d) partials per row (at most ceil(V / 64)).

@@ -195,7 +195,8 @@ Layout plan(const pd_model& M, int max_batch, int max_src, int max_tgt) {
 
 struct GraphKey {
   int mode, block, horizon, max_iters, B, R_max, slot, fused;
-  int long_keys;   // rows of more than one key chunk possible: 1 self-attention, 2 cross-attention
+  int long_keys;   // attention's launch choice: rows of more than one key chunk possible (1 self-attention,
+                   // 2 cross-attention), 4 16-row tiles
   // the trace buffers are kernel arguments of a traced iteration
   const void* trace;
   long long trace_cap;
@@ -255,6 +256,7 @@ struct pd_ctx {
   // host bounds on the key count of any row: the longest encoded source, and
   // the longest target of the running decode (or debug_logits' T)
   int src_keys = 0, self_keys = 0;
+  int sent_rows = 0;                   // host bound on the decoder rows of one sentence (the block, or T)
   bool encoded = false;
 
   template <typename T> T* at(size_t off) const { return reinterpret_cast<T*>(ws + off); }
@@ -415,6 +417,7 @@ hipError_t decoder_pass(pd_ctx& C, const Rows& r, float* logits, hipStream_t s, 
                 a_buf, d, 1.0f / std::sqrt(static_cast<float>(M.dh))};
     aa.out_feed = feed;
     aa.max_keys = C.self_keys;
+    aa.sent_rows = C.sent_rows; aa.st = C.at<SentState>(C.L.st); aa.n_sent = C.enc_B;
     if ((e = launch_attn(M.dt, aa, r.R_max, s)) != hipSuccess) return e;
 
     g = gemm_base(r);
@@ -437,6 +440,7 @@ hipError_t decoder_pass(pd_ctx& C, const Rows& r, float* logits, hipStream_t s, 
                   C.at<int>(C.L.src_len), a_buf, d, 1.0f / std::sqrt(static_cast<float>(M.dh))};
     aa.out_feed = feed;
     aa.max_keys = C.src_keys;
+    aa.sent_rows = C.sent_rows; aa.st = C.at<SentState>(C.L.st); aa.n_sent = C.enc_B;
     if ((e = launch_attn(M.dt, aa, r.R_max, s)) != hipSuccess) return e;
 
     g = gemm_base(r);
@@ -559,6 +563,7 @@ hipError_t encoder_pass(pd_ctx& C, const int32_t* src, int B, int n_max, const i
     // cross-attention this measured slower for the large model: slots past
     // the source come from HBM there, not from the cache the encoder filled)
     aa.one_source = B == 1 ? 1 : 0;
+    aa.sent_rows = n_max;
     if ((e = launch_attn(M.dt, aa, R, s)) != hipSuccess) return e;
     g = gemm_base(r);
     g.x = a_buf; g.ldx = d; g.w = M.enc(l, E_WO); g.wp = M.enc_feed(l, E_WO); g.bias = M.enc(l, E_BO); g.N = d; g.K = d;
@@ -994,6 +999,7 @@ pd_status pd_decode_init(pd_ctx* ctx, int32_t mode, int32_t block, int32_t horiz
     if (st != PD_OK) return st;
   }
   C.self_keys = m_max;
+  C.sent_rows = Lmax;
 
   CtrlArgs ca;
   std::memset(&ca, 0, sizeof(ca));
@@ -1061,7 +1067,8 @@ pd_status pd_decode_init(pd_ctx* ctx, int32_t mode, int32_t block, int32_t horiz
     if (e == hipSuccess) {
       if (C.use_graphs && slot < 0) {   // iterations timed with events are launched directly
         hipGraphExec_t ex = nullptr;
-        const int long_keys = (C.self_keys > kAttnChunkKeys ? 1 : 0) | (C.src_keys > kAttnChunkKeys ? 2 : 0);
+        const int long_keys = (C.self_keys > kAttnChunkKeys ? 1 : 0) | (C.src_keys > kAttnChunkKeys ? 2 : 0) |
+                              (attn_tiled(M.dh, M.H, Lmax, Rb) ? 4 : 0);
         const GraphKey key{key_mode, block, horizon, max_iters, B, Rb, slot, fused ? 1 : 0, long_keys, C.trace,
                            C.trace_cap, C.trace_part};
         e = iteration_graph(C, key, r, cb, &ex);
@@ -1196,6 +1203,7 @@ pd_status pd_debug_logits(pd_ctx* ctx, const int32_t* tgt_in, int32_t T, float* 
   const int R = B * T;
   Rows r{nullptr, R, RowMap{nullptr, nullptr, T}, tgt_in, R};
   ctx->self_keys = T;
+  ctx->sent_rows = T;
   hipError_t e = decoder_pass(*ctx, r, logits, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(PD_E_DEVICE, std::string("decoder launch: ") + hipGetErrorString(e));
   return PD_OK;

@@ -1,0 +1,85 @@
+"""The kernels of launches with many rows give bitwise the rows of the few-row
+kernels (whose values the oracle tests judge): teacher-forced logits of a
+ragged batch against each sentence alone in at most 16 rows, at the edges of
+row tiles, key chunks and column tiles."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2305_10427_amd import configs as C, pdec, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def cfg_of(dtype, d, heads, d_ff, vocab=333, pre_ln=True):
+    return dataclasses.replace(C.TINY, name=f"rows_{dtype}_{d}_{heads}", n_enc=1, n_dec=2, d_model=d, n_heads=heads,
+                               d_ff=d_ff, vocab=vocab, pre_ln=pre_ln, act_gelu=pre_ln, dtype=dtype)
+
+
+def logits(ctx, src, lens, tgt):
+    import torch
+    ctx.encode(torch.from_numpy(src).cuda(), lens)
+    return ctx.debug_logits(torch.from_numpy(tgt)).cpu().numpy()
+
+
+def compare(cfg, B, n, T, seed=1, plant=None):
+    """Logits of B sentences of T positions against the same prefix evaluated 16 rows at a time at most."""
+    w = synth.make_weights(cfg, seed=seed, bias_std=0.3, ln_std=0.2)
+    if plant is not None:                       # a token whose embedding is not finite
+        w.values["emb"][plant] = np.nan
+        if w.bf16_bits is not None:
+            w.bf16_bits["emb"][plant] = 0x7fc0
+    gm = pdec.Model(cfg, w)
+    g = np.random.default_rng(seed)
+    lens = [int(x) for x in np.linspace(1, n, B).round()]
+    src = g.integers(4, cfg.vocab - 1, (B, n)).astype(np.int32)
+    tgt = g.integers(4, cfg.vocab - 1, (B, T)).astype(np.int32)
+    tgt[:, 0] = C.BOS_ID
+    if plant is not None:
+        tgt[:, T // 2] = plant                  # positions before it must not see it
+    got = logits(pdec.Context(gm, B, n, T), src, lens, tgt)
+    one = pdec.Context(gm, 1, n, T)
+    t = min(T, 16)
+    for b in range(0, B, max(1, B // 7)):
+        want = logits(one, src[b:b + 1, :lens[b]], lens[b:b + 1], tgt[b:b + 1, :t])
+        np.testing.assert_array_equal(got[b, :t], want[0])
+    if plant is not None:
+        assert np.isfinite(got[:, :T // 2, :plant]).all() and not np.isfinite(got[:, T // 2]).any()
+    return got
+
+
+@pytest.mark.parametrize("dtype,d,heads,d_ff", [("bf16", 256, 8, 512), ("bf16", 256, 4, 2048), ("bf16", 256, 2, 256),
+                                                ("f32", 128, 4, 256), ("f32", 256, 4, 2048), ("f32", 256, 2, 256),
+                                                ("f32", 64, 4, 256)])
+@pytest.mark.parametrize("B,n,T", [(2, 16, 17), (35, 65, 31), (70, 130, 16), (33, 20, 33)])
+def test_teacher_forced_rows_are_bitwise_those_of_few_rows(dtype, d, heads, d_ff, B, n, T):
+    compare(cfg_of(dtype, d, heads, d_ff), B, n, T)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_a_later_rows_nan_stays_out_of_earlier_rows(dtype):
+    cfg = cfg_of(dtype, 128, 2, 256)
+    compare(cfg, 45, 20, 24, plant=cfg.vocab - 1)
+
+
+@pytest.mark.parametrize("dtype,heads", [("bf16", 4), ("bf16", 8), ("f32", 2)])
+@pytest.mark.parametrize("mode,block", [("gs_jacobi", 8), ("gs_jacobi", 19), ("jacobi", 1)])
+def test_blocks_across_row_tiles_equal_single_decodes(dtype, heads, mode, block):
+    """Blocks whose rows straddle 16-row tiles (several sentences a tile, unequal lengths)."""
+    import torch
+    cfg = cfg_of(dtype, 256, heads, 512, pre_ln=False)
+    gm = pdec.Model(cfg, synth.make_weights(cfg, seed=4, bias_std=0.5, ln_std=0.3))
+    B, n = 70, 70
+    g = np.random.default_rng(2)
+    src = g.integers(4, cfg.vocab, (B, n)).astype(np.int32)
+    lens = [70, 3, 66, 20, 64, 1, 41] * 10
+    ms = [67, 21, 9, 40, 5, 64, 33] * 10
+    ctx, one = pdec.Context(gm, B, n, 80), pdec.Context(gm, 1, n, 80)
+    ctx.encode(torch.from_numpy(src).cuda(), lens)
+    ids, ln, k, fl = [t.cpu().numpy() for t in ctx.decode(mode, ms, block=block)]
+    for b in range(0, B, 11):
+        one.encode(torch.from_numpy(src[b:b + 1, :lens[b]]).cuda(), lens[b:b + 1])
+        i1, l1, k1, f1 = [t.cpu().numpy() for t in one.decode("gs_jacobi", ms[b:b + 1], block=min(block, 7))]
+        assert ln[b] == l1[0] and fl[b] == f1[0]
+        np.testing.assert_array_equal(ids[b, :ln[b]], i1[0, :l1[0]])
