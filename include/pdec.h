@@ -150,9 +150,9 @@ pd_status pd_weight_shape(const pd_config* cfg, int32_t idx, int64_t* rows, int6
  * caller keeps them allocated and unchanged until pd_model_destroy.  No
  * device work happens here.  The first pd_ctx_create on the model allocates,
  * on the current device, a copy of every encoder and decoder matrix
- * product's weights (w_qkv, w_o, w1, w2; ca_w_q, ca_w_o) and of the token
+ * product's weights (w_qkv, w_o, w1, w2; ca_w_q, ca_w_kv, ca_w_o) and of the token
  * embedding E (the vocabulary projection's weights) rearranged into the
- * order in which the few-row kernels feed the matrix cores (as many bytes as
+ * order in which the kernels feed the matrix cores (as many bytes as
  * those matrices, E's rows rounded up to a multiple of 16; freed by
  * pd_model_destroy).  Returns PD_E_ARG for
  * a null / misaligned pointer or a wrong count, PD_E_UNSUPPORTED for shapes

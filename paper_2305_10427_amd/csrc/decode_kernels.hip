@@ -585,7 +585,7 @@ __global__ __launch_bounds__(256) void k_embed(EmbedArgs a) {
 
 // ---------------------------------------------------------------------------
 // Row LayerNorm, one wave per row, with the statistics and element split of
-// the LayerNorm prologue of the products (ln_row_stats, ln_row_apply), so a
+// the LayerNorm prologue of the products (ln_row_stats, ln_apply), so a
 // row is normalised bitwise alike here and there.
 template <typename WT, typename XT, int NT>
 __global__ __launch_bounds__(256) void k_ln(LnArgs a) {
@@ -597,8 +597,19 @@ __global__ __launch_bounds__(256) void k_ln(LnArgs a) {
   ln_row_load<XT, NT>(h, static_cast<const XT*>(a.x) + static_cast<size_t>(row) * a.d, a.d, lane, true);
   float mean, rstd;
   ln_row_stats<XT, NT>(h, a.d, a.eps, mean, rstd);
-  ln_row_apply<WT, XT, NT>(h, a.d, mean, rstd, static_cast<const WT*>(a.g), static_cast<const WT*>(a.b),
-                           static_cast<WT*>(a.out) + static_cast<size_t>(row) * a.d, nullptr, lane);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int k0 = 8 * lane + 512 * t;
+    if (k0 < a.d) {
+      float gv[8], bv[8], y[8];
+      load_n<WT, 8>(static_cast<const WT*>(a.g), k0, gv);
+      load_n<WT, 8>(static_cast<const WT*>(a.b), k0, bv);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = ln_apply(h.get(t, e), mean, rstd, gv[e], bv[e]);
+      if (a.out != nullptr) store8<WT>(static_cast<WT*>(a.out), static_cast<size_t>(row) * a.d + k0, y);
+      if (a.feed != nullptr) store_row8<WT>(static_cast<WT*>(a.feed), row, k0, a.d, 0, y);
+    }
+  }
 }
 
 // Largest logit and log-sum-exp of each row from the vocabulary kernel's

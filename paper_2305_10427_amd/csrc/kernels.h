@@ -181,7 +181,8 @@ struct LnArgs {
   const void* b;
   float eps;
   int d;
-  void* out;               // storage type
+  void* out;               // storage type, row-major (nullptr: not written)
+  void* feed;              // storage type, MFMA feed order (feed_index; nullptr: not written)
 };
 
 // One record of the decoding trace: the token an iteration produced at a
@@ -305,6 +306,16 @@ void gemm_tiled_init();
 hipError_t launch_gemm_tiled(int epi, int ksplit, const GemmArgs& a, hipStream_t s);
 int gemm_tiled_cfg(int epi, int N, int rows);
 hipError_t launch_gemm_tiled_cfg(int epi, int ksplit, int cfg, const GemmArgs& a, hipStream_t s);
+// Products of many rows and the vocabulary projection of more than 16 rows
+// without LDS staging: weights from their feed-order copy (wp; lw of a
+// multi-layer launch), inputs in feed order (x_feed) or row-major; bitwise the
+// same values as launch_gemm.  The argmax writes gemm_feed_parts(N, K, rows)
+// partials per row.
+hipError_t gemm_feed_init();   // once before the first launch
+int gemm_feed_cfg(int epi, int N, int K, int rows);
+int gemm_feed_parts(int V, int K, int rows);
+hipError_t launch_gemm_feed(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s);
+hipError_t launch_gemm_feed_cfg(int dtype, int epi, int ksplit, int cfg, const GemmArgs& a, hipStream_t s);
 // Whether launch_attn evaluates 16 rows of a head together on the matrix cores
 // (bitwise the same rows): sentences of up to sent_rows rows, launch bound R_max.
 bool attn_tiled(int dh, int heads, int sent_rows, int R_max);

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.h"
+#include "kernels.h"
 
 namespace pdec {
 
@@ -67,6 +68,23 @@ template <> struct Mma<float> {
   static __device__ __forceinline__ void unpack(frag f, float* v) { v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w; }
   static __device__ __forceinline__ frag pack(const float* v) { return make_float4(v[0], v[1], v[2], v[3]); }
 };
+
+// Eight consecutive values (col a multiple of 8) of a row in the storage type:
+// row-major with leading dimension ld, or (feed_k > 0) in the feed order of a
+// [rows][feed_k] matrix.
+template <typename T>
+__device__ __forceinline__ void store_row8(T* p, int row, int col, int feed_k, int ld, const float* v) {
+  if (feed_k == 0) {
+    store8<T>(p, static_cast<size_t>(row) * ld + col, v);
+  } else if constexpr (sizeof(T) == 2) {
+    store8<T>(p, feed_index<Mma<T>::KS, Mma<T>::EPL>(row, col, feed_k), v);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; e += 4)
+      *reinterpret_cast<float4*>(p + feed_index<Mma<T>::KS, Mma<T>::EPL>(row, col + e, feed_k)) =
+          make_float4(v[e], v[e + 1], v[e + 2], v[e + 3]);
+  }
+}
 
 // max(v, 0) that keeps a NaN (fmaxf would return 0 for it and hide a
 // non-finite value from the argmax's check).

@@ -282,27 +282,33 @@ GemmArgs gemm_base(const Rows& r) {
   return g;
 }
 
-// One matrix product.  pro_ln: normalise x (float if x_f32) with (lg, lb)
-// first; for many rows the LayerNorm runs as its own kernel into ln_tmp.
-hipError_t run_gemm(pd_ctx& C, const Rows& r, GemmArgs g, int epi, bool pro_ln, void* ln_tmp,
+// Whether an iteration's products run on the many-row kernel (gemm_feed),
+// every LayerNorm as its own kernel writing the feed order it reads.
+bool many_rows(const pd_model& M, int R_max) { return R_max > stream_max_rows(M.d); }
+
+// One matrix product of the layers.  pro_ln: normalise x (float if x_f32) with
+// (lg, lb) first; for many rows the LayerNorm runs as its own kernel into
+// feed_tmp (feed order; g.ln_out also gets the rows).
+hipError_t run_gemm(pd_ctx& C, const Rows& r, GemmArgs g, int epi, bool pro_ln, void* feed_tmp,
                     hipStream_t s) {
   const pd_model& M = *C.M;
   int pro = PRO_NONE;
+  const bool many = many_rows(M, r.R_max);
   if (pro_ln) {
-    if (r.R_max <= stream_max_rows(M.d)) {
+    if (!many) {
       pro = PRO_LN;
     } else {
-      LnArgs la{r.n_dev, r.n_host, g.x, g.x_f32, g.ln_g, g.ln_b, M.cfg.ln_eps, g.K, ln_tmp};
+      LnArgs la{r.n_dev, r.n_host, g.x, g.x_f32, g.ln_g, g.ln_b, M.cfg.ln_eps, g.K, g.ln_out, feed_tmp};
       hipError_t e = launch_ln(M.dt, la, r.R_max, s);
       if (e != hipSuccess) return e;
-      g.x = ln_tmp;
+      g.x = feed_tmp;
       g.x_f32 = 0;
-      g.ldx = g.K;
+      g.x_feed = 1;
       g.ln_out = nullptr;
     }
   }
   const int ksplit = (epi == EPI_ARGMAX || epi == EPI_LOGITS) ? 1 : (g.K >= 2048 ? 8 : 4);
-  if (r.R_max > stream_max_rows(M.d) && gemm_tiled_ok(M.dt, pro, g)) return launch_gemm_tiled(epi, ksplit, g, s);
+  if (many) return launch_gemm_feed(M.dt, epi, ksplit, g, s);
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   if (C.gemm_slot >= 0) {   // a timed decoder product: the next event pair of the slot, and its bytes
     const int sl = C.gemm_slot;
@@ -331,10 +337,11 @@ hipError_t run_gemm(pd_ctx& C, const Rows& r, GemmArgs g, int epi, bool pro_ln, 
 // (vocab_grid partials per row); larger ones the product kernel's argmax
 // epilogue (one partial per 64-column workgroup).
 constexpr int kVocabStreamMaxRows = 16;
-// Above one row tile the vocabulary argmax runs on the tiled product kernel
-// (after a separate LayerNorm) when it supports the shape.
+// Above one row tile the vocabulary argmax runs after a separate LayerNorm, on
+// the tiled product kernel (bf16 rows of more than 512 elements) or the
+// feed-order one.
 bool vocab_tiled(const pd_model& M, int R_max) {
-  if (R_max <= kVocabStreamMaxRows) return false;
+  if (R_max <= kVocabStreamMaxRows || M.d <= 512) return false;
   GemmArgs g;
   std::memset(&g, 0, sizeof(g));
   g.N = M.V;
@@ -350,7 +357,7 @@ int vocab_parts(const pd_model& M, int R_max) {
     const int bn = gemm_tiled_bn(EPI_ARGMAX, M.V, R_max);
     return (M.V + bn - 1) / bn;
   }
-  return gemm_grid(EPI_ARGMAX, M.V, 1);
+  return gemm_feed_parts(M.V, M.d, R_max);
 }
 
 // Decoder pass over the rows of one iteration (or the teacher-forced rows of
@@ -392,7 +399,8 @@ hipError_t decoder_pass(pd_ctx& C, const Rows& r, float* logits, hipStream_t s, 
   // rows the row-major loads, which repeat rows, cost about the same or less:
   // large model, 16 rows: 650.6 -> 616.9 us per iteration; MT-base, 5 rows:
   // 204.5 -> 206.4)
-  const int feed = r.R_max > 8 && r.R_max <= 16 ? 1 : 0;
+  // iterations of many rows pass them in that order too
+  const int feed = (r.R_max > 8 && r.R_max <= 16) || many_rows(M, r.R_max) ? 1 : 0;
   for (int l = 0; l < cfg.n_dec; ++l) {
     // self-attention: Q -> q_buf, K/V of the block -> cache (layer l)
     GemmArgs g = gemm_base(r);
@@ -410,8 +418,7 @@ hipError_t decoder_pass(pd_ctx& C, const Rows& r, float* logits, hipStream_t s, 
     g.out_f32 = q_buf; g.ldo = d; g.q_cols = d;
     g.kc = C.at<char>(C.L.self_k) + l * self_layer; g.vc = C.at<char>(C.L.self_v) + l * self_layer;
     g.H = M.H; g.dh = M.dh; g.T = C.max_tgt; g.d = d;
-    // post-LN with a separate LayerNorm kernel writes the residual stream itself
-    if ((e = run_gemm(C, r, g, EPI_QKV, ln_qkv, pre ? a_buf : x_res, s)) != hipSuccess) return e;
+    if ((e = run_gemm(C, r, g, EPI_QKV, ln_qkv, a_buf, s)) != hipSuccess) return e;
 
     AttnArgs aa{r.n_dev, r.n_host, q_buf, d, g.kc, g.vc, M.H, M.dh, C.max_tgt, r.map, 1, nullptr,
                 a_buf, d, 1.0f / std::sqrt(static_cast<float>(M.dh))};
@@ -433,7 +440,7 @@ hipError_t decoder_pass(pd_ctx& C, const Rows& r, float* logits, hipStream_t s, 
     else { g.x = s_buf; g.x_f32 = 1; g.ln_g = M.dec(l, D_LN1G); g.ln_b = M.dec(l, D_LN1B); g.ln_out = x_res; g.ldlo = d; }
     g.ldx = d; g.ln_eps = cfg.ln_eps;
     g.w = M.dec(l, D_CWQ); g.wp = M.dec_feed(l, D_CWQ); g.bias = M.dec(l, D_CBQ); g.N = d; g.K = d; g.out_f32 = q_buf; g.ldo = d;
-    if ((e = run_gemm(C, r, g, EPI_F32, true, pre ? a_buf : x_res, s)) != hipSuccess) return e;
+    if ((e = run_gemm(C, r, g, EPI_F32, true, a_buf, s)) != hipSuccess) return e;
 
     aa = AttnArgs{r.n_dev, r.n_host, q_buf, d, C.at<char>(C.L.cross_k) + l * cross_layer,
                   C.at<char>(C.L.cross_v) + l * cross_layer, M.H, M.dh, C.max_src, r.map, 0,
@@ -457,7 +464,7 @@ hipError_t decoder_pass(pd_ctx& C, const Rows& r, float* logits, hipStream_t s, 
     g.ldx = d; g.ln_eps = cfg.ln_eps;
     g.w = M.dec(l, D_W1); g.wp = M.dec_feed(l, D_W1); g.bias = M.dec(l, D_B1); g.N = M.dff; g.K = d;
     g.out = h_buf; g.ldo = M.dff; g.act = cfg.act_gelu ? 2 : 1; g.out_feed = feed;
-    if ((e = run_gemm(C, r, g, EPI_ACT, true, pre ? a_buf : x_res, s)) != hipSuccess) return e;
+    if ((e = run_gemm(C, r, g, EPI_ACT, true, a_buf, s)) != hipSuccess) return e;
 
     g = gemm_base(r);
     g.x = h_buf; g.ldx = M.dff; g.x_feed = feed; g.w = M.dec(l, D_W2); g.wp = M.dec_feed(l, D_W2); g.bias = M.dec(l, D_B2); g.N = d; g.K = M.dff;
@@ -475,6 +482,7 @@ hipError_t decoder_pass(pd_ctx& C, const Rows& r, float* logits, hipStream_t s, 
   g.w = M.w[0]; g.bias = M.w[1]; g.N = M.V; g.K = d; g.logit_scale = cfg.logit_scale;
   if (logits != nullptr) {
     g.out_f32 = logits; g.ldo = M.V;
+    g.wp = M.feed[0];
     return run_gemm(C, r, g, EPI_LOGITS, true, a_buf, s);
   }
   g.partials = C.at<uint2>(C.L.partials);
@@ -482,19 +490,20 @@ hipError_t decoder_pass(pd_ctx& C, const Rows& r, float* logits, hipStream_t s, 
   g.part_lse = C.trace_part;   // nullptr unless tracing
   const int n_parts = vocab_parts(M, r.R_max);
   const bool tiled = r.R_max > kVocabStreamMaxRows && vocab_tiled(M, r.R_max);
-  if (tiled) {   // the final LayerNorm as its own kernel, outside the timed vocabulary launch
-    LnArgs la{r.n_dev, r.n_host, g.x, g.x_f32, g.ln_g, g.ln_b, cfg.ln_eps, d, a_buf};
+  if (r.R_max > kVocabStreamMaxRows) {   // the final LayerNorm as its own kernel, outside the timed vocabulary launch
+    LnArgs la{r.n_dev, r.n_host, g.x, g.x_f32, g.ln_g, g.ln_b, cfg.ln_eps, d, tiled ? a_buf : nullptr,
+              tiled ? nullptr : a_buf};
     if ((e = launch_ln(M.dt, la, r.R_max, s)) != hipSuccess) return e;
-    g.x = a_buf; g.x_f32 = 0; g.ldx = d;
+    g.x = a_buf; g.x_f32 = 0; g.ldx = d; g.x_feed = tiled ? 0 : 1;
   }
+  g.wp = M.feed[0];
   if (r.R_max <= kVocabStreamMaxRows) {
     // one row tile: streaming kernel (E from its feed-order copy), timed by its
     // own dispatch timestamps
-    g.wp = M.feed[0];
     e = launch_vocab_argmax(M.dt, g, s, slot >= 0 ? C.tv0[slot] : nullptr, slot >= 0 ? C.tv1[slot] : nullptr);
   } else {
     if (slot >= 0 && (e = hipEventRecord(C.tv0[slot], s)) != hipSuccess) return e;
-    e = tiled ? launch_gemm_tiled(EPI_ARGMAX, 1, g, s) : run_gemm(C, r, g, EPI_ARGMAX, true, a_buf, s);
+    e = tiled ? launch_gemm_tiled(EPI_ARGMAX, 1, g, s) : launch_gemm_feed(M.dt, EPI_ARGMAX, 1, g, s);
     if (e == hipSuccess && slot >= 0) e = hipEventRecord(C.tv1[slot], s);
   }
   if (e != hipSuccess) return e;
@@ -524,6 +533,7 @@ hipError_t encoder_pass(pd_ctx& C, const int32_t* src, int B, int n_max, const i
   const size_t es = M.dt == DT_BF16 ? 2 : 4;
   const size_t cross_layer = static_cast<size_t>(C.max_batch) * C.max_src * d * es;
   const int R = B * n_max;
+  const int feed = many_rows(M, R) ? 1 : 0;   // activations between the kernels in feed order
   Rows r{nullptr, R, RowMap{nullptr, nullptr, n_max}, src, R};
   const int* klen = C.at<int>(C.L.src_len);
   const float scale = 1.0f / std::sqrt(static_cast<float>(M.dh));
@@ -542,12 +552,11 @@ hipError_t encoder_pass(pd_ctx& C, const int32_t* src, int B, int n_max, const i
   for (int l = 0; l < cfg.n_enc; ++l) {
     GemmArgs g = gemm_base(r);
     bool ln = true;
-    void* ln_tmp = a_buf;
     if (pre) {
       g.x = x_res; g.x_f32 = 0; g.ln_g = M.enc(l, E_LN1G); g.ln_b = M.enc(l, E_LN1B);
     } else if (l > 0) {
       g.x = s_buf; g.x_f32 = 1; g.ln_g = M.enc(l - 1, E_LN2G); g.ln_b = M.enc(l - 1, E_LN2B);
-      g.ln_out = x_res; g.ldlo = d; ln_tmp = x_res;
+      g.ln_out = x_res; g.ldlo = d;
     } else {
       g.x = x_res; g.x_f32 = 0; ln = false;   // the embedding
     }
@@ -556,7 +565,7 @@ hipError_t encoder_pass(pd_ctx& C, const int32_t* src, int B, int n_max, const i
     g.out_f32 = q_buf; g.ldo = d; g.q_cols = d;
     g.kc = C.at<char>(C.L.enc_k); g.vc = C.at<char>(C.L.enc_v);
     g.H = M.H; g.dh = M.dh; g.T = C.max_src; g.d = d;
-    if ((e = run_gemm(C, r, g, EPI_QKV, ln, ln_tmp, s)) != hipSuccess) return e;
+    if ((e = run_gemm(C, r, g, EPI_QKV, ln, a_buf, s)) != hipSuccess) return e;
     AttnArgs aa{nullptr, R, q_buf, d, g.kc, g.vc, M.H, M.dh, C.max_src, r.map, 0, klen, a_buf, d, scale};
     aa.max_keys = C.src_keys;
     // one source: its key slots load with the queries (in the decoder's
@@ -564,26 +573,26 @@ hipError_t encoder_pass(pd_ctx& C, const int32_t* src, int B, int n_max, const i
     // the source come from HBM there, not from the cache the encoder filled)
     aa.one_source = B == 1 ? 1 : 0;
     aa.sent_rows = n_max;
+    aa.out_feed = feed;
     if ((e = launch_attn(M.dt, aa, R, s)) != hipSuccess) return e;
     g = gemm_base(r);
-    g.x = a_buf; g.ldx = d; g.w = M.enc(l, E_WO); g.wp = M.enc_feed(l, E_WO); g.bias = M.enc(l, E_BO); g.N = d; g.K = d;
+    g.x = a_buf; g.ldx = d; g.x_feed = feed; g.w = M.enc(l, E_WO); g.wp = M.enc_feed(l, E_WO); g.bias = M.enc(l, E_BO); g.N = d; g.K = d;
     g.resid = x_res; g.ldr = d; g.ldo = d;
     if (pre) g.out = x_res; else g.out_f32 = s_buf;
     if ((e = run_gemm(C, r, g, EPI_RESID, false, nullptr, s)) != hipSuccess) return e;
     g = gemm_base(r);
     if (pre) {
       g.x = x_res; g.x_f32 = 0; g.ln_g = M.enc(l, E_LN2G); g.ln_b = M.enc(l, E_LN2B);
-      ln_tmp = a_buf;
     } else {
       g.x = s_buf; g.x_f32 = 1; g.ln_g = M.enc(l, E_LN1G); g.ln_b = M.enc(l, E_LN1B);
-      g.ln_out = x_res; g.ldlo = d; ln_tmp = x_res;
+      g.ln_out = x_res; g.ldlo = d;
     }
     g.ldx = d; g.ln_eps = cfg.ln_eps;
     g.w = M.enc(l, E_W1); g.wp = M.enc_feed(l, E_W1); g.bias = M.enc(l, E_B1); g.N = M.dff; g.K = d;
-    g.out = h_buf; g.ldo = M.dff; g.act = cfg.act_gelu ? 2 : 1;
-    if ((e = run_gemm(C, r, g, EPI_ACT, true, ln_tmp, s)) != hipSuccess) return e;
+    g.out = h_buf; g.ldo = M.dff; g.act = cfg.act_gelu ? 2 : 1; g.out_feed = feed;
+    if ((e = run_gemm(C, r, g, EPI_ACT, true, a_buf, s)) != hipSuccess) return e;
     g = gemm_base(r);
-    g.x = h_buf; g.ldx = M.dff; g.w = M.enc(l, E_W2); g.wp = M.enc_feed(l, E_W2); g.bias = M.enc(l, E_B2); g.N = d; g.K = M.dff;
+    g.x = h_buf; g.ldx = M.dff; g.x_feed = feed; g.w = M.enc(l, E_W2); g.wp = M.enc_feed(l, E_W2); g.bias = M.enc(l, E_B2); g.N = d; g.K = M.dff;
     g.resid = x_res; g.ldr = d; g.ldo = d;
     if (pre) g.out = x_res; else g.out_f32 = s_buf;
     if ((e = run_gemm(C, r, g, EPI_RESID, false, nullptr, s)) != hipSuccess) return e;
@@ -598,14 +607,14 @@ hipError_t encoder_pass(pd_ctx& C, const int32_t* src, int B, int n_max, const i
     if (pre) { g.x = x_res; g.x_f32 = 0; g.ln_g = M.enc_ln(0); g.ln_b = M.enc_ln(1); }
     else { g.x = s_buf; g.x_f32 = 1; g.ln_g = M.enc(cfg.n_enc - 1, E_LN2G); g.ln_b = M.enc(cfg.n_enc - 1, E_LN2B); }
     g.ln_eps = cfg.ln_eps;
-    g.ldx = d; g.w = M.dec(l0, D_CWKV); g.bias = M.dec(l0, D_CBKV); g.N = 2 * d; g.K = d;
+    g.ldx = d; g.w = M.dec(l0, D_CWKV); g.wp = feed ? M.dec_feed(l0, D_CWKV) : nullptr; g.bias = M.dec(l0, D_CBKV); g.N = 2 * d; g.K = d;
     g.q_cols = 0;
     g.kc = C.at<char>(C.L.cross_k) + l0 * cross_layer; g.vc = C.at<char>(C.L.cross_v) + l0 * cross_layer;
     g.H = M.H; g.dh = M.dh; g.T = C.max_src; g.d = d;
     g.n_layers = nl;
     g.kv_stride = static_cast<long long>(cross_layer);
     for (int z = 0; z < nl; ++z) {
-      g.lw[z] = M.dec(l0 + z, D_CWKV);
+      g.lw[z] = feed ? M.dec_feed(l0 + z, D_CWKV) : M.dec(l0 + z, D_CWKV);
       g.lb[z] = M.dec(l0 + z, D_CBKV);
     }
     if ((e = run_gemm(C, r, g, EPI_QKV, true, a_buf, s)) != hipSuccess) return e;
@@ -778,7 +787,7 @@ static hipError_t make_feed(const pd_model& M) {
   for (int l = 0; l < M.cfg.n_enc; ++l)
     for (int j : {E_WQKV, E_WO, E_W1, E_W2}) prods.push_back(2 + 12 * l + j);
   for (int l = 0; l < M.cfg.n_dec; ++l)
-    for (int j : {D_WQKV, D_WO, D_CWQ, D_CWO, D_W1, D_W2}) prods.push_back(M.dec_base() + 20 * l + j);
+    for (int j : {D_WQKV, D_WO, D_CWQ, D_CWKV, D_CWO, D_W1, D_W2}) prods.push_back(M.dec_base() + 20 * l + j);
   const size_t es = M.dt == DT_BF16 ? 2 : 4;
   hipError_t e = hipSuccess;
   for (int idx : prods) {
@@ -811,6 +820,7 @@ pd_status pd_model_create(const pd_config* cfg, const void* const* dev_weights, 
     if (dev_weights[i] == nullptr || !aligned(dev_weights[i], 16))
       return fail(PD_E_ARG, "weight " + std::to_string(i) + " is null or not 16-byte aligned");
   gemm_tiled_init();
+  if (gemm_feed_init() != hipSuccess) (void)hipGetLastError();   // no device here: the first launch reports it
   pd_model* m = new pd_model();
   m->cfg = *cfg;
   m->w.assign(dev_weights, dev_weights + n);
