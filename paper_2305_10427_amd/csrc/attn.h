@@ -102,13 +102,6 @@ __device__ __forceinline__ float upper_half(float v) {
   return __uint_as_float(r[1]);
 }
 
-// Orders the wave's LDS writes before its following reads.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // One chunk's own softmax statistics and unnormalised output: m_c, l_c and
 // o_c (lane l < 32: dimensions 2l, 2l + 1 (+ 64 i)).
 template <int DH> struct ChunkOut {

@@ -1,6 +1,6 @@
 // Matrix products of launches with many rows (batched sentences times block
 // positions, teacher-forced rows, batched encoder rows) and the vocabulary
-// projection of more than 16 rows, on MFMA without LDS staging.
+// projection of some tens of rows, on MFMA without LDS staging.
 //
 // Y[r][n] = sum_k X[r][k] * W[n][k] (+ the epilogues of k_gemm).  Both operands
 // are read in the MFMA feed order (a wave-wide load is 1 KB contiguous: the 16
@@ -35,6 +35,7 @@
 #include <cstring>
 
 #include "common.h"
+#include "epilogue.h"
 #include "kernels.h"
 #include "mma.h"
 
@@ -170,32 +171,9 @@ __global__ __launch_bounds__(64 * KW * WM * WN) void k_gemm_feed(GemmArgs a, int
 #pragma unroll
         for (int w = 1; w < KW; ++w) t = t + *reinterpret_cast<const floatx4_t*>(p + w * BM * LD + e);   // range order
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[e + i] = t[i] + bias_v[e + i];
+        for (int i = 0; i < 4; ++i) v[e + i] = t[i];
       }
-      if constexpr (EPI == EPI_F32) {
-        store8<float>(a.out_f32, static_cast<size_t>(row) * a.ldo + col, v);
-      } else if constexpr (EPI == EPI_ACT) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (a.act == 2) ? gelu_erf(v[e]) : relu(v[e]);
-        store_row8<WT>(static_cast<WT*>(a.out), row, col, a.out_feed ? N : 0, a.ldo, v);
-      } else if constexpr (EPI == EPI_RESID) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = v[e] + rv[e];
-        if (a.out_f32 != nullptr) store8<float>(a.out_f32, static_cast<size_t>(row) * a.ldo + col, v);
-        else store8<WT>(static_cast<WT*>(a.out), static_cast<size_t>(row) * a.ldo + col, v);
-      } else if constexpr (EPI == EPI_QKV) {
-        if (col < a.q_cols) {
-          store8<float>(a.out_f32, static_cast<size_t>(row) * a.ldo + col, v);
-        } else {
-          const int c = col - a.q_cols;
-          const int which = c / a.d;
-          const int cc = c - which * a.d;
-          const int hh = cc / a.dh;
-          const int dd = cc - hh * a.dh;
-          const size_t idx = ((static_cast<size_t>(sent) * a.H + hh) * a.T + pos) * a.dh + dd;
-          store8<WT>(static_cast<WT*>(which == 0 ? a.kc : a.vc), idx, v);
-        }
-      }
+      finish8<WT, EPI>(a, row, col, v, bias_v, rv, sent, pos);
     }
   } else {
     // lane holds C[4 lg + e][lr] of each subtile
@@ -274,10 +252,8 @@ __global__ __launch_bounds__(64 * KW * WM * WN) void k_gemm_feed(GemmArgs a, int
 
 namespace {
 
-// Tile configurations.  Products: subtiles per wave (K split over the waves);
-// vocabulary: subtiles per wave and waves along rows and columns.
+// Tile configurations of the products: subtiles per wave (K split over the waves).
 enum ProductCfg { P_32x32 = 0, P_32x64, P_64x64, P_COUNT };
-enum VocabCfg { V_32x256 = 0, V_64x256, V_128x128, V_128x256, V_COUNT };
 
 template <typename WT, int EPI, int FM, int FN, int KW, int WM, int WN, int D>
 hipError_t launch_shape(const GemmArgs& a, hipStream_t s, bool init) {
@@ -306,15 +282,9 @@ hipError_t launch_product(const GemmArgs& a, int cfg, hipStream_t s, bool init) 
   }
 }
 
-template <typename WT, int EPI>
-hipError_t launch_vocab(const GemmArgs& a, int cfg, hipStream_t s, bool init) {
-  switch (cfg) {
-    case V_32x256: return launch_shape<WT, EPI, 2, 4, 1, 1, 4, 4>(a, s, init);
-    case V_64x256: return launch_shape<WT, EPI, 4, 4, 1, 1, 4, 2>(a, s, init);
-    case V_128x128: return launch_shape<WT, EPI, 4, 4, 1, 2, 2, 2>(a, s, init);
-    case V_128x256: return launch_shape<WT, EPI, 8, 4, 1, 1, 4, 2>(a, s, init);
-    default: return hipErrorInvalidValue;
-  }
+// The vocabulary: 32 rows x 256 columns, four waves side by side.
+template <typename WT, int EPI> hipError_t launch_vocab(const GemmArgs& a, hipStream_t s, bool init) {
+  return launch_shape<WT, EPI, 2, 4, 1, 1, 4, 4>(a, s, init);
 }
 
 template <typename WT>
@@ -324,8 +294,8 @@ hipError_t launch_w(int epi, int ksplit, int cfg, const GemmArgs& a, hipStream_t
     case EPI_ACT: return ksplit == 8 ? launch_product<WT, EPI_ACT, 8>(a, cfg, s, init) : launch_product<WT, EPI_ACT, 4>(a, cfg, s, init);
     case EPI_RESID: return ksplit == 8 ? launch_product<WT, EPI_RESID, 8>(a, cfg, s, init) : launch_product<WT, EPI_RESID, 4>(a, cfg, s, init);
     case EPI_QKV: return ksplit == 8 ? launch_product<WT, EPI_QKV, 8>(a, cfg, s, init) : launch_product<WT, EPI_QKV, 4>(a, cfg, s, init);
-    case EPI_ARGMAX: return launch_vocab<WT, EPI_ARGMAX>(a, cfg, s, init);
-    case EPI_LOGITS: return launch_vocab<WT, EPI_LOGITS>(a, cfg, s, init);
+    case EPI_ARGMAX: return launch_vocab<WT, EPI_ARGMAX>(a, s, init);
+    case EPI_LOGITS: return launch_vocab<WT, EPI_LOGITS>(a, s, init);
     default: return hipErrorInvalidValue;
   }
 }
@@ -346,24 +316,14 @@ hipError_t gemm_feed_init() {
   return hipSuccess;
 }
 
-int gemm_feed_cfg(int epi, int N, int K, int rows) {
-  if (epi == EPI_ARGMAX || epi == EPI_LOGITS) {
-    if (rows <= 32 || K <= 512) return V_32x256;
-    if (rows <= 64) return V_64x256;
-    return V_128x128;
-  }
+static int gemm_feed_cfg(int N, int rows) {
   const auto wgs = [&](int bm, int bn) { return ((rows + bm - 1) / bm) * ((N + bn - 1) / bn); };
   if (wgs(64, 64) >= 256) return P_64x64;
   if (wgs(32, 64) >= 256) return P_32x64;
   return P_32x32;
 }
 
-int gemm_feed_parts(int V, int K, int rows) {
-  const int bn = gemm_feed_cfg(EPI_ARGMAX, V, K, rows) == V_128x128 ? 128 : 256;
-  return (V + bn - 1) / bn;
-}
-
-hipError_t launch_gemm_feed_cfg(int dtype, int epi, int ksplit, int cfg, const GemmArgs& a, hipStream_t s) {
+hipError_t launch_gemm_feed(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s) {
   if (a.n_rows <= 0) return hipSuccess;
   const int es = dtype == DT_BF16 ? 2 : 4, ks = dtype == DT_BF16 ? Mma<bf16_t>::KS : Mma<float>::KS;
   const bool vocab = epi == EPI_ARGMAX || epi == EPI_LOGITS;
@@ -373,14 +333,9 @@ hipError_t launch_gemm_feed_cfg(int dtype, int epi, int ksplit, int cfg, const G
   if (256ull * std::max(a.ldx, a.K) * es >= (1ull << 31)) return hipErrorInvalidValue;
   if (a.out_feed && (epi != EPI_ACT || a.N % 32 != 0)) return hipErrorInvalidValue;
   if (!(epi == EPI_QKV && a.n_layers > 1) && a.wp == nullptr) return hipErrorInvalidValue;
+  const int cfg = gemm_feed_cfg(a.N, a.n_rows);
   return dtype == DT_BF16 ? launch_w<bf16_t>(epi, ksplit, cfg, a, s, false)
                           : launch_w<float>(epi, ksplit, cfg, a, s, false);
-}
-
-hipError_t launch_gemm_feed(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s) {
-  const int cfg = gemm_feed_cfg(epi, a.N, a.K, a.n_rows);
-  if (epi == EPI_ARGMAX && a.part_ld < gemm_feed_parts(a.N, a.K, a.n_rows)) return hipErrorInvalidValue;
-  return launch_gemm_feed_cfg(dtype, epi, ksplit, cfg, a, s);
 }
 
 }  // namespace pdec

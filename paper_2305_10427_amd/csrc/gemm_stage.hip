@@ -1,0 +1,421 @@
+// The vocabulary projection of many rows (batched sentences times block
+// positions, teacher-forced rows) on MFMA with both operands staged through LDS
+// by direct loads.
+//
+// logit[r][n] = s * (sum_k X[r][k] * W[n][k]) + bias[n], as the fused argmax
+// (EPI_ARGMAX) or stored (EPI_LOGITS).  X and W are in the MFMA feed order, so a
+// stage of one MFMA step is BM / 16 + BN / 16 blocks of 1 KB: each block is one
+// wave-wide 16-byte load that lands in LDS without passing through registers,
+// and one conflict-free wave-wide LDS read per use.  A wave owns FM x FN
+// subtiles of 16 x 16.
+//
+// Bound and split: read straight into registers (k_gemm_feed) a 64 x 64 wave
+// tile moves 8 KB through the 64-byte-a-cycle vector cache per 16 matrix
+// instructions, half of the matrix rate at best; staged through registers
+// (row-major tiles, the kernel this one replaces) the LDS stores took the
+// issue slots and a 256-column tile did not fit.  Here a block comes through
+// the cache once per workgroup and the waves' reads go to LDS (128 bytes a
+// cycle): 64 x 128 per wave of a 128 x 256 tile needs 48 + 24 KB of LDS traffic
+// per 512 matrix cycles.  NS stages are in the ring; the fragments of stage
+// s + 1 are read while stage s is multiplied, and stage s + NS is requested as
+// soon as the barrier says that every wave has read stage s: one barrier per
+// stage, and several workgroups per CU to fill the gaps.
+// 250,027 x 1024, argmax of 64 / 128 / 256 / 512 / 1024 / 2048 rows: 101 / 145 /
+// 252 / 481 / 940 / 1811 us -> 92 / 95 / 154 / 275 / 508 / 913 us (1148 TFLOP/s);
+// logits of 952 / 4160 rows 989 / 4131 -> 715 / 2796 us (4.2 GB stored).
+//
+// Every logit is accumulated from zero in increasing k, as in the streaming
+// vocabulary kernel: a row's values depend neither on the kernel, nor on the
+// tile slot, nor on the other rows of the call.
+//
+// Tile order for the eight XCDs as in k_gemm_feed (row blocks fastest, eight
+// contiguous chunks).  Rows at or above the device row count are not stored; a
+// workgroup whose rows all lie there returns at once.
+#include <algorithm>
+#include <cstring>
+
+#include "common.h"
+#include "kernels.h"
+#include "mma.h"
+
+namespace pdec {
+
+namespace {
+
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kBlock = kWave * 16;         // bytes of one operand block (16 rows or columns, one MFMA step)
+constexpr int kOutPad = 4;                 // floats of padding per row of an output subtile in LDS
+
+// Raw buffer resource of n bytes at p (32-bit data format, no swizzle, no index), wave-uniform.
+__device__ __forceinline__ i32x4_t buffer_of(const char* p, uint32_t n) {
+  const uint64_t u = reinterpret_cast<uint64_t>(p);
+  return i32x4_t{__builtin_amdgcn_readfirstlane(static_cast<int>(u)),
+                 __builtin_amdgcn_readfirstlane(static_cast<int>(u >> 32) & 0xffff),
+                 __builtin_amdgcn_readfirstlane(static_cast<int>(n)), 0x00020000};
+}
+
+// 16 bytes per lane from r[voff + soff] to LDS lds + 16 lane (no register is
+// written; completion is counted by vmcnt, waited for in stage_wait).
+__device__ __forceinline__ void load_to_lds(i32x4_t r, uint32_t voff, uint32_t soff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory");
+}
+
+// All but the N youngest loads of this wave have landed and its LDS reads are
+// done; then the workgroup's barrier.
+template <int N> __device__ __forceinline__ void stage_wait() {
+  static_assert(N <= 63, "vmcnt");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
+}
+
+// The same with `later` stages (at most MAX; wave-uniform) of LPS loads each left in flight.
+template <int MAX, int LPS> __device__ __forceinline__ void stage_wait_for(int later) {
+  if constexpr (MAX > 0) {
+    if (later < MAX) return stage_wait_for<MAX - 1, LPS>(later);
+  }
+  stage_wait<MAX * LPS>();
+}
+
+}  // namespace
+
+template <typename WT, int EPI, int FM, int FN, int WM, int WN, int NS>
+__global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_stage(GemmArgs a, int n_rb, int n_tiles) {
+  using MM = Mma<WT>;
+  using frag = typename MM::frag;
+  constexpr int KS = MM::KS;
+  constexpr int ES = static_cast<int>(sizeof(WT));
+  constexpr int NW = WM * WN, NT = 64 * NW;
+  constexpr int BM = 16 * FM * WM, BN = 16 * FN * WN;
+  constexpr int TA = BM / 16, TB = BN / 16, NB = TA + TB;   // blocks of a stage
+  static_assert(TA % NW == 0 && TB % NW == 0, "whole blocks per wave");
+  constexpr int LA = TA / NW, LB = TB / NW, LPS = LA + LB;  // loads per wave and stage
+  constexpr uint32_t STAGE = NB * kBlock;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int wm = wave / WN, wn = wave % WN;
+  const int lr = lane & 15, lg = lane >> 4;
+
+  const int L = blockIdx.x;
+  const int xcd = L & 7, q8 = n_tiles >> 3, rem = n_tiles & 7;
+  const int tile = xcd * q8 + min(xcd, rem) + (L >> 3);
+  const int cb = tile / n_rb, rb = tile - cb * n_rb;
+  const int m0 = rb * BM, n0 = cb * BN;
+  const int R_max = a.n_rows, K = a.K, N = a.N;
+  const int R = a.n_rows_dev ? *a.n_rows_dev : a.n_rows;
+  if (m0 >= R) return;                                   // workgroup-uniform
+  const int n = K / KS;                                  // MFMA steps = stages
+
+  // the tile's operand blocks: subtiles past the last repeat it (every read lies inside its buffer)
+  const char* wf = static_cast<const char*>(a.wp);
+  const size_t tile_bytes = static_cast<size_t>(16) * K * ES;
+  const int rts = min(TA, (R_max + 15) / 16 - m0 / 16), cts = min(TB, (N + 15) / 16 - n0 / 16);
+  const i32x4_t xr = buffer_of(static_cast<const char*>(a.x) + (m0 / 16) * tile_bytes,
+                               rts * static_cast<uint32_t>(tile_bytes));
+  const i32x4_t wr = buffer_of(wf + (n0 / 16) * tile_bytes, cts * static_cast<uint32_t>(tile_bytes));
+  extern __shared__ __align__(16) unsigned char s_dyn[];
+  const uint32_t lds0 = static_cast<uint32_t>(
+      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)(s_dyn)));
+  uint32_t ga[LA], gb[LB];                               // this wave's blocks: byte offsets of their first step
+#pragma unroll
+  for (int u = 0; u < LA; ++u) ga[u] = static_cast<uint32_t>(min(wave + NW * u, rts - 1)) * static_cast<uint32_t>(tile_bytes);
+#pragma unroll
+  for (int u = 0; u < LB; ++u) gb[u] = static_cast<uint32_t>(min(wave + NW * u, cts - 1)) * static_cast<uint32_t>(tile_bytes);
+  const uint32_t voff = lane * 16;
+  auto issue = [&](int s, uint32_t buf) __attribute__((always_inline)) {
+    const uint32_t at = lds0 + buf + wave * kBlock, ks = static_cast<uint32_t>(s) * kBlock;
+#pragma unroll
+    for (int u = 0; u < LA; ++u) load_to_lds(xr, voff, ga[u] + ks, at + u * NW * kBlock);
+#pragma unroll
+    for (int u = 0; u < LB; ++u) load_to_lds(wr, voff, gb[u] + ks, at + (TA + u * NW) * kBlock);
+  };
+  struct Frags {
+    frag a[FM], b[FN];
+  };
+  Frags f0, f1;
+  const unsigned char* pa = s_dyn + wm * FM * kBlock + lane * 16;
+  const unsigned char* pb = s_dyn + (TA + wn * FN) * kBlock + lane * 16;
+  auto read = [&](Frags& f, uint32_t buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i) f.a[i] = *reinterpret_cast<const frag*>(pa + buf + i * kBlock);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) f.b[j] = *reinterpret_cast<const frag*>(pb + buf + j * kBlock);
+  };
+
+  floatx4_t acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+    if (s < n) issue(s, s * STAGE);
+  stage_wait_for<NS - 1, LPS>(n - 1);
+  read(f0, 0);
+  uint32_t cur = 0;                                      // LDS offset of stage s
+  auto step_row = [&](const Frags& f, int i) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = MM::step(f.a[i], f.b[j], acc[i][j]);
+  };
+  // Stage s with every ring slot still to be refilled.  The requests and the
+  // fragment reads are spread between the matrix instructions (a wave issues
+  // in order: all of them up front leave its matrix unit idle meanwhile).
+  auto iter = [&](int s, const Frags& f, Frags& fn) __attribute__((always_inline)) {
+    const uint32_t nxt = cur == (NS - 1) * STAGE ? 0 : cur + STAGE;
+    stage_wait<(NS - 2) * LPS>();                        // stage s + 1 has landed, every wave has read stage s
+    const uint32_t at = lds0 + cur + wave * kBlock, ks = static_cast<uint32_t>(s + NS) * kBlock;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+#pragma unroll
+      for (int u = (FM + FN) * i / FM; u < (FM + FN) * (i + 1) / FM; ++u) {
+        if (u < FM) fn.a[u] = *reinterpret_cast<const frag*>(pa + nxt + u * kBlock);
+        else fn.b[u - FM] = *reinterpret_cast<const frag*>(pb + nxt + (u - FM) * kBlock);
+      }
+#pragma unroll
+      for (int u = LPS * i / FM; u < LPS * (i + 1) / FM; ++u) {
+        if (u < LA) load_to_lds(xr, voff, ga[u] + ks, at + u * NW * kBlock);
+        else load_to_lds(wr, voff, gb[u - LA] + ks, at + (TA + (u - LA) * NW) * kBlock);
+      }
+      step_row(f, i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    cur = nxt;
+  };
+  auto last = [&](int s, const Frags& f, Frags& fn) __attribute__((always_inline)) {
+    const uint32_t nxt = cur == (NS - 1) * STAGE ? 0 : cur + STAGE;
+    if (s + 1 < n) {
+      stage_wait_for<NS - 2, LPS>(n - 2 - s);
+      if (s + NS < n) issue(s + NS, cur);
+      read(fn, nxt);
+    }
+#pragma unroll
+    for (int i = 0; i < FM; ++i) step_row(f, i);
+    cur = nxt;
+  };
+  int s0 = 0;
+  for (; s0 + 1 + NS < n; s0 += 2) {
+    iter(s0, f0, f1);
+    iter(s0 + 1, f1, f0);
+  }
+  for (; s0 + 1 < n; s0 += 2) {
+    last(s0, f0, f1);
+    last(s0 + 1, f1, f0);
+  }
+  if (s0 < n) last(s0, f0, f1);
+  __syncthreads();                                       // the stages are dead: LDS holds outputs from here
+
+  if constexpr (EPI == EPI_ARGMAX) {
+    // lane holds C[4 lg + e][lr] of each subtile
+    float bias_v[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+      bias_v[j] = Elt<WT>::load(static_cast<const WT*>(a.bias), min(n0 + (wn * FN + j) * 16 + lr, N - 1));
+    uint32_t* s_key = reinterpret_cast<uint32_t*>(s_dyn);          // [WN][BM]
+    uint32_t* s_idx = s_key + WN * BM;
+    float2* s_lse = reinterpret_cast<float2*>(s_idx + WN * BM);
+    const bool want_lse = a.part_lse != nullptr;
+    // Whole column tiles without a log-sum-exp compare the logits as floats:
+    // five instructions a logit.  A non-finite logit, or a best of zero (whose
+    // sign the order keys tell apart), sends the wave's row group to the keys.
+    const bool whole = n0 + BN <= N && !want_lse;
+    const uint32_t c0 = static_cast<uint32_t>(n0 + wn * FN * 16 + lr);
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int rl = (wm * FM + i) * 16 + 4 * lg + e;
+        uint32_t bk = 0u, bi = 0x7fffffffu, nf = 0u;
+        float best = -INFINITY, chk = 0.f;
+        int bj = 0;
+        if (whole) {
+#pragma unroll
+          for (int j = 0; j < FN; ++j) {
+            const float logit = fmaf(a.logit_scale, acc[i][j][e], bias_v[j]);   // s * (h . E[col]) + bias[col]
+            chk = fmaf(logit, 0.f, chk);                 // NaN once a logit is not finite
+            const bool t = logit > best;
+            best = t ? logit : best;
+            bj = t ? j : bj;
+          }
+        }
+        if (whole && __builtin_amdgcn_ballot_w64(!(chk == 0.f) || best == 0.f) == 0) {
+          const float mx = group16_max(best);
+          bi = best == mx ? c0 + 16u * bj : 0x7fffffffu;
+          bi = min(bi, dpp_u<kDppXor1>(bi));
+          bi = min(bi, dpp_u<kDppXor2>(bi));
+          bi = min(bi, dpp_u<kDppHalfMirror>(bi));
+          bi = min(bi, dpp_u<kDppMirror>(bi));
+          bk = float_key(mx);
+        } else {
+          float lm = -INFINITY, ls = 0.f;
+#pragma unroll
+          for (int j = 0; j < FN; ++j) {
+            const uint32_t col = c0 + 16u * j;
+            const float logit = fmaf(a.logit_scale, acc[i][j][e], bias_v[j]);
+            if (col < static_cast<uint32_t>(N)) {
+              if (!isfinite(logit)) nf = 1u;
+              else {
+                best_take(bk, bi, float_key(logit), col);
+                if (want_lse) lse_take(lm, ls, logit);
+              }
+            }
+          }
+          group16_best(bk, bi);
+          nf = group16_or(nf);
+          if (want_lse) {
+            group16_lse(lm, ls);
+            if (lr == 0) s_lse[wn * BM + rl] = make_float2(lm, ls);
+          }
+        }
+        if (lr == 0) {
+          s_key[wn * BM + rl] = bk;
+          s_idx[wn * BM + rl] = bi | (nf << 31);
+        }
+      }
+    __syncthreads();
+    for (int t = tid; t < BM; t += NT) {
+      if (m0 + t >= R) break;
+      uint32_t kk = s_key[t], ii = s_idx[t] & 0x7fffffffu, ff = s_idx[t] >> 31;
+#pragma unroll
+      for (int w = 1; w < WN; ++w) {
+        best_take(kk, ii, s_key[w * BM + t], s_idx[w * BM + t] & 0x7fffffffu);
+        ff |= s_idx[w * BM + t] >> 31;
+      }
+      a.partials[static_cast<size_t>(m0 + t) * a.part_ld + cb] = make_uint2(kk, ii | (ff << 31));
+      if (want_lse) {
+        float m = s_lse[t].x, sm = s_lse[t].y;
+#pragma unroll
+        for (int w = 1; w < WN; ++w) lse_merge(m, sm, s_lse[w * BM + t].x, s_lse[w * BM + t].y);   // wave order
+        a.part_lse[static_cast<size_t>(m0 + t) * a.part_ld + cb] = make_float2(m, sm);
+      }
+    }
+  } else {
+    // 16 rows at a time through this wave's slice of LDS, so that a lane
+    // stores consecutive columns of a row
+    constexpr int LD = 16 * FN + kOutPad;
+    float* part = reinterpret_cast<float*>(s_dyn) + wave * 16 * LD;
+    const int nw = n0 + wn * FN * 16, mw = m0 + wm * FM * 16;
+    auto to_lds = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part[(4 * lg + e) * LD + 16 * j + lr] = acc[i][j][e];
+      wave_lds_sync();
+    };
+    if constexpr (EPI == EPI_LOGITS) {
+      float bias_l[FN / 4];
+#pragma unroll
+      for (int u = 0; u < FN / 4; ++u)
+        bias_l[u] = Elt<WT>::load(static_cast<const WT*>(a.bias), min(nw + 64 * u + lane, N - 1));
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        if (mw + 16 * i >= R) break;                     // wave-uniform
+        to_lds(i);
+        for (int r = 0; r < 16; ++r) {
+          if (mw + 16 * i + r >= R) break;
+          float* out = a.out_f32 + static_cast<size_t>(mw + 16 * i + r) * a.ldo + nw;
+#pragma unroll
+          for (int u = 0; u < FN / 4; ++u)
+            if (nw + 64 * u + lane < N) out[64 * u + lane] = fmaf(a.logit_scale, part[r * LD + 64 * u + lane], bias_l[u]);
+        }
+        wave_lds_sync();                                 // the next subtile overwrites the slice
+      }
+    }
+  }
+}
+
+namespace {
+
+// Tiles (rows x columns of a workgroup) and ring depths.
+enum StageCfg { S_NONE = -1, S_64x256 = 0, S_128x128, S_128x256, S_256x256, S_COUNT };
+
+template <typename WT, int EPI, int FM, int FN, int WM, int WN, int NS>
+hipError_t launch_shape(const GemmArgs& a, hipStream_t s, bool init) {
+  constexpr int BM = 16 * FM * WM, BN = 16 * FN * WN, NW = WM * WN;
+  constexpr size_t stages = static_cast<size_t>(NS) * (BM + BN) / 16 * kBlock;
+  constexpr size_t outs = EPI == EPI_ARGMAX ? 16ull * WN * BM : 4ull * NW * 16 * (16 * FN + kOutPad);
+  constexpr size_t lds = stages > outs ? stages : outs;
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
+  const int n_rb = (a.n_rows + BM - 1) / BM;
+  const int n_tiles = n_rb * ((a.N + BN - 1) / BN);
+  auto kernel = &k_gemm_stage<WT, EPI, FM, FN, WM, WN, NS>;
+  if (init) {          // gfx950 has 160 KB of LDS per CU
+    if (lds <= 65536) return hipSuccess;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               static_cast<int>(lds));
+  }
+  hipLaunchKernelGGL(kernel, dim3(n_tiles), dim3(64 * NW), lds, s, a, n_rb, n_tiles);
+  return hipGetLastError();
+}
+
+template <typename WT, int EPI> hipError_t launch_cfg(const GemmArgs& a, int cfg, hipStream_t s, bool init) {
+  if (cfg == S_128x256) return launch_shape<WT, EPI, 4, 8, 2, 2, 3>(a, s, init);
+  if constexpr (std::is_same<WT, bf16_t>::value) {
+    if (cfg == S_64x256) return launch_shape<WT, EPI, 4, 4, 1, 4, 4>(a, s, init);
+    if (cfg == S_128x128) return launch_shape<WT, EPI, 4, 4, 2, 2, 3>(a, s, init);
+    if constexpr (EPI == EPI_LOGITS)
+      if (cfg == S_256x256) return launch_shape<WT, EPI, 8, 4, 2, 4, 4>(a, s, init);
+  }
+  return init ? hipSuccess : hipErrorInvalidValue;
+}
+
+template <typename WT> hipError_t launch_w(int epi, int cfg, const GemmArgs& a, hipStream_t s, bool init) {
+  return epi == EPI_ARGMAX ? launch_cfg<WT, EPI_ARGMAX>(a, cfg, s, init) : launch_cfg<WT, EPI_LOGITS>(a, cfg, s, init);
+}
+
+// The tile for a vocabulary projection of `rows` rows, S_NONE where k_gemm_feed
+// is the faster one (or as fast).  Measured, us: bf16 250,027 x 1024, argmax:
+// 32 rows feed 91, 64x256 92; 64 rows 64x256 92, 128x128 94 (feed 105); 128 rows
+// 128x128 95, 64x256 106; 256 rows 154 / 128x256 157; 400 rows 128x256 270,
+// 128x128 288; 1024 rows 508 / 562.  58,101 x 512: 128 rows feed 23, 128x128 22;
+// 160 rows 28 / 30; 200 rows 34 / 30; 1000 rows 121 / 76 (128x256 81).  Stored
+// logits: 300 rows of 1024 128x256 249, 256x256 336; 500 rows 364 / 326 (fuller
+// rows of 256 columns go out together), 4160 rows 3319 / 2796; 400 rows of 512
+// 128x128 44, 256x256 45, feed 53; 1000 rows 130 / 100 / 200.  float32 of 512 (matrix bound: 157
+// TFLOP/s): 300 rows feed 171, 128x256 210; 1120 rows 597 / 527, logits 622 / 574.
+int stage_cfg(int dtype, int epi, int K, int rows) {
+  if (dtype == DT_F32) return rows > 512 ? S_128x256 : S_NONE;
+  if (K <= 512) {
+    if (rows <= (epi == EPI_LOGITS ? 64 : 160)) return S_NONE;
+    return epi == EPI_LOGITS && rows > 512 ? S_256x256 : S_128x128;
+  }
+  if (rows <= 32) return S_NONE;
+  if (rows <= 64) return S_64x256;
+  if (epi == EPI_LOGITS) return rows > 448 ? S_256x256 : S_128x256;
+  return rows <= 256 ? S_128x128 : S_128x256;
+}
+
+}  // namespace
+
+// The configurations whose stages exceed 64 KB of LDS are allowed it here, once.
+hipError_t gemm_stage_init() {
+  GemmArgs a;
+  memset(&a, 0, sizeof(a));
+  for (int epi : {EPI_ARGMAX, EPI_LOGITS})
+    for (int cfg = 0; cfg < S_COUNT; ++cfg) {
+      hipError_t e = launch_w<bf16_t>(epi, cfg, a, nullptr, true);
+      if (e == hipSuccess) e = launch_w<float>(epi, cfg, a, nullptr, true);
+      if (e != hipSuccess) return e;
+    }
+  return hipSuccess;
+}
+
+int vocab_rows_parts(int dtype, int V, int K, int rows) {
+  const int bn = stage_cfg(dtype, EPI_ARGMAX, K, rows) == S_128x128 ? 128 : 256;   // k_gemm_feed: 256
+  return (V + bn - 1) / bn;
+}
+
+hipError_t launch_vocab_rows(int dtype, int epi, const GemmArgs& a, hipStream_t s) {
+  if (a.n_rows <= 0) return hipSuccess;
+  if (epi != EPI_ARGMAX && epi != EPI_LOGITS) return hipErrorInvalidValue;
+  if (epi == EPI_ARGMAX && a.part_ld < vocab_rows_parts(dtype, a.N, a.K, a.n_rows)) return hipErrorInvalidValue;
+  const int cfg = stage_cfg(dtype, epi, a.K, a.n_rows);
+  if (cfg == S_NONE) return launch_gemm_feed(dtype, epi, 1, a, s);
+  const int es = dtype == DT_BF16 ? 2 : 4, ks = dtype == DT_BF16 ? Mma<bf16_t>::KS : Mma<float>::KS;
+  if (a.K % ks != 0 || a.x_f32 || !a.x_feed || a.wp == nullptr) return hipErrorInvalidValue;
+  if (256ull * a.K * es >= (1ull << 31)) return hipErrorInvalidValue;   // byte offsets within a tile fit 31 bits
+  return dtype == DT_BF16 ? launch_w<bf16_t>(epi, cfg, a, s, false) : launch_w<float>(epi, cfg, a, s, false);
+}
+
+}  // namespace pdec

@@ -297,25 +297,18 @@ int gemm_grid(int epi, int N, int ksplit);
 // K % KS == 0, else hipErrorInvalidValue.
 hipError_t launch_pack_feed(int dtype, const void* w, void* out, int N, int K, hipStream_t s);
 size_t gemm_ln_lds_bytes(int K, size_t elt);
-// Products of many rows on LDS-staged MFMA tiles (bf16, no prologue, K a
-// multiple of 64); bitwise the same values as launch_gemm.  The vocabulary
-// argmax writes ceil(N / gemm_tiled_bn(EPI_ARGMAX, N, rows)) partials per row.
-bool gemm_tiled_ok(int dtype, int pro, const GemmArgs& a);
-int gemm_tiled_bn(int epi, int N, int rows);
-void gemm_tiled_init();
-hipError_t launch_gemm_tiled(int epi, int ksplit, const GemmArgs& a, hipStream_t s);
-int gemm_tiled_cfg(int epi, int N, int rows);
-hipError_t launch_gemm_tiled_cfg(int epi, int ksplit, int cfg, const GemmArgs& a, hipStream_t s);
 // Products of many rows and the vocabulary projection of more than 16 rows
 // without LDS staging: weights from their feed-order copy (wp; lw of a
 // multi-layer launch), inputs in feed order (x_feed) or row-major; bitwise the
-// same values as launch_gemm.  The argmax writes gemm_feed_parts(N, K, rows)
-// partials per row.
+// same values as launch_gemm.  The argmax writes ceil(N / 256) partials per row.
 hipError_t gemm_feed_init();   // once before the first launch
-int gemm_feed_cfg(int epi, int N, int K, int rows);
-int gemm_feed_parts(int V, int K, int rows);
 hipError_t launch_gemm_feed(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s);
-hipError_t launch_gemm_feed_cfg(int dtype, int epi, int ksplit, int cfg, const GemmArgs& a, hipStream_t s);
+// The vocabulary projection (EPI_ARGMAX, EPI_LOGITS) of more than 16 rows in
+// feed order, on the kernel that suits the rows; the argmax writes
+// vocab_rows_parts(dtype, N, K, rows) partials per row (at most ceil(N / 64)).
+hipError_t gemm_stage_init();  // once before the first launch
+int vocab_rows_parts(int dtype, int V, int K, int rows);
+hipError_t launch_vocab_rows(int dtype, int epi, const GemmArgs& a, hipStream_t s);
 // Whether launch_attn evaluates 16 rows of a head together on the matrix cores
 // (bitwise the same rows): sentences of up to sent_rows rows, launch bound R_max.
 bool attn_tiled(int dh, int heads, int sent_rows, int R_max);

@@ -286,6 +286,12 @@ GemmArgs gemm_base(const Rows& r) {
 // every LayerNorm as its own kernel writing the feed order it reads.
 bool many_rows(const pd_model& M, int R_max) { return R_max > stream_max_rows(M.d); }
 
+// Iterations of at most one 16-row tile use the streaming vocabulary kernel
+// (vocab_grid partials per row); above it the vocabulary projection runs after
+// a separate LayerNorm, on launch_vocab_rows (stored logits of 48 rows: 250,027
+// x 1024 295 -> 102 us, 58,101 x 512 36 -> 13 us against the general kernel).
+constexpr int kVocabStreamMaxRows = 16;
+
 // One matrix product of the layers.  pro_ln: normalise x (float if x_f32) with
 // (lg, lb) first; for many rows the LayerNorm runs as its own kernel into
 // feed_tmp (feed order; g.ln_out also gets the rows).
@@ -293,7 +299,8 @@ hipError_t run_gemm(pd_ctx& C, const Rows& r, GemmArgs g, int epi, bool pro_ln, 
                     hipStream_t s) {
   const pd_model& M = *C.M;
   int pro = PRO_NONE;
-  const bool many = many_rows(M, r.R_max);
+  const bool vocab = epi == EPI_LOGITS && r.R_max > kVocabStreamMaxRows;
+  const bool many = vocab || many_rows(M, r.R_max);
   if (pro_ln) {
     if (!many) {
       pro = PRO_LN;
@@ -307,7 +314,8 @@ hipError_t run_gemm(pd_ctx& C, const Rows& r, GemmArgs g, int epi, bool pro_ln, 
       g.ln_out = nullptr;
     }
   }
-  const int ksplit = (epi == EPI_ARGMAX || epi == EPI_LOGITS) ? 1 : (g.K >= 2048 ? 8 : 4);
+  if (vocab) return launch_vocab_rows(M.dt, epi, g, s);
+  const int ksplit = epi == EPI_LOGITS ? 1 : (g.K >= 2048 ? 8 : 4);
   if (many) return launch_gemm_feed(M.dt, epi, ksplit, g, s);
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   if (C.gemm_slot >= 0) {   // a timed decoder product: the next event pair of the slot, and its bytes
@@ -333,31 +341,8 @@ hipError_t run_gemm(pd_ctx& C, const Rows& r, GemmArgs g, int epi, bool pro_ln, 
   return launch_gemm(M.dt, pro, epi, ksplit, g, s, ev0, ev1);
 }
 
-// Iterations of at most one 16-row tile use the streaming vocabulary kernel
-// (vocab_grid partials per row); larger ones the product kernel's argmax
-// epilogue (one partial per 64-column workgroup).
-constexpr int kVocabStreamMaxRows = 16;
-// Above one row tile the vocabulary argmax runs after a separate LayerNorm, on
-// the tiled product kernel (bf16 rows of more than 512 elements) or the
-// feed-order one.
-bool vocab_tiled(const pd_model& M, int R_max) {
-  if (R_max <= kVocabStreamMaxRows || M.d <= 512) return false;
-  GemmArgs g;
-  std::memset(&g, 0, sizeof(g));
-  g.N = M.V;
-  g.K = M.d;
-  g.ldx = M.d;
-  g.n_rows = R_max;
-  return gemm_tiled_ok(M.dt, PRO_NONE, g);
-}
-
 int vocab_parts(const pd_model& M, int R_max) {
-  if (R_max <= kVocabStreamMaxRows) return vocab_grid(M.dt, M.V, M.d);
-  if (vocab_tiled(M, R_max)) {
-    const int bn = gemm_tiled_bn(EPI_ARGMAX, M.V, R_max);
-    return (M.V + bn - 1) / bn;
-  }
-  return gemm_feed_parts(M.V, M.d, R_max);
+  return R_max <= kVocabStreamMaxRows ? vocab_grid(M.dt, M.V, M.d) : vocab_rows_parts(M.dt, M.V, M.d, R_max);
 }
 
 // Decoder pass over the rows of one iteration (or the teacher-forced rows of
@@ -489,12 +474,10 @@ hipError_t decoder_pass(pd_ctx& C, const Rows& r, float* logits, hipStream_t s, 
   g.part_ld = gemm_grid(EPI_ARGMAX, M.V, 1);
   g.part_lse = C.trace_part;   // nullptr unless tracing
   const int n_parts = vocab_parts(M, r.R_max);
-  const bool tiled = r.R_max > kVocabStreamMaxRows && vocab_tiled(M, r.R_max);
   if (r.R_max > kVocabStreamMaxRows) {   // the final LayerNorm as its own kernel, outside the timed vocabulary launch
-    LnArgs la{r.n_dev, r.n_host, g.x, g.x_f32, g.ln_g, g.ln_b, cfg.ln_eps, d, tiled ? a_buf : nullptr,
-              tiled ? nullptr : a_buf};
+    LnArgs la{r.n_dev, r.n_host, g.x, g.x_f32, g.ln_g, g.ln_b, cfg.ln_eps, d, nullptr, a_buf};
     if ((e = launch_ln(M.dt, la, r.R_max, s)) != hipSuccess) return e;
-    g.x = a_buf; g.x_f32 = 0; g.ldx = d; g.x_feed = tiled ? 0 : 1;
+    g.x = a_buf; g.x_f32 = 0; g.ldx = d; g.x_feed = 1;
   }
   g.wp = M.feed[0];
   if (r.R_max <= kVocabStreamMaxRows) {
@@ -503,7 +486,7 @@ hipError_t decoder_pass(pd_ctx& C, const Rows& r, float* logits, hipStream_t s, 
     e = launch_vocab_argmax(M.dt, g, s, slot >= 0 ? C.tv0[slot] : nullptr, slot >= 0 ? C.tv1[slot] : nullptr);
   } else {
     if (slot >= 0 && (e = hipEventRecord(C.tv0[slot], s)) != hipSuccess) return e;
-    e = tiled ? launch_gemm_tiled(EPI_ARGMAX, 1, g, s) : launch_gemm_feed(M.dt, EPI_ARGMAX, 1, g, s);
+    e = launch_vocab_rows(M.dt, EPI_ARGMAX, g, s);
     if (e == hipSuccess && slot >= 0) e = hipEventRecord(C.tv1[slot], s);
   }
   if (e != hipSuccess) return e;
@@ -819,8 +802,8 @@ pd_status pd_model_create(const pd_config* cfg, const void* const* dev_weights, 
   for (int i = 0; i < n; ++i)
     if (dev_weights[i] == nullptr || !aligned(dev_weights[i], 16))
       return fail(PD_E_ARG, "weight " + std::to_string(i) + " is null or not 16-byte aligned");
-  gemm_tiled_init();
-  if (gemm_feed_init() != hipSuccess) (void)hipGetLastError();   // no device here: the first launch reports it
+  if (gemm_feed_init() != hipSuccess || gemm_stage_init() != hipSuccess)
+    (void)hipGetLastError();   // no device here: the first launch reports it
   pd_model* m = new pd_model();
   m->cfg = *cfg;
   m->w.assign(dev_weights, dev_weights + n);

@@ -83,3 +83,34 @@ def test_blocks_across_row_tiles_equal_single_decodes(dtype, heads, mode, block)
         i1, l1, k1, f1 = [t.cpu().numpy() for t in one.decode("gs_jacobi", ms[b:b + 1], block=min(block, 7))]
         assert ln[b] == l1[0] and fl[b] == f1[0]
         np.testing.assert_array_equal(ids[b, :ln[b]], i1[0, :l1[0]])
+
+
+@pytest.mark.parametrize("dtype,d,heads,vocab", [("bf16", 640, 10, 1111), ("bf16", 96, 6, 1111), ("f32", 96, 6, 1111)])
+@pytest.mark.parametrize("B,T", [(1, 17), (2, 32), (5, 13), (4, 75), (4, 113), (9, 57), (40, 20)])
+def test_vocabulary_rows_are_bitwise_those_of_few_rows(dtype, d, heads, vocab, B, T):
+    """Row counts around each change of the projection's tile (16, 32, 64, 160, 448, 512 rows), a ragged last column tile."""
+    compare(cfg_of(dtype, d, heads, 128, vocab=vocab), B, 7, T)
+
+
+@pytest.mark.parametrize("dtype,d,heads", [("bf16", 640, 10), ("bf16", 128, 2), ("f32", 128, 2)])
+@pytest.mark.parametrize("B,m", [(1, 17), (3, 16), (5, 13), (9, 28), (9, 60)])
+def test_argmax_of_planted_logits(dtype, d, heads, B, m):
+    """Logits that are the output bias alone (scale 0): the largest, the lowest index among equals (at zero too,
+    where the order of +0 and -0 must not matter), and the flag of a non-finite one."""
+    import torch
+    cfg = dataclasses.replace(cfg_of(dtype, d, heads, 128, vocab=1111), logit_scale=0.0)
+    for best, at, bad in [(2.5, (700, 701, 1110), None), (0.0, (300, 555, 1030), None), (1.0, (1110,), None),
+                          (0.5, (513,), 20)]:
+        w = synth.make_weights(cfg, seed=3)
+        bias = np.full(cfg.vocab, -1.0, np.float32)
+        bias[list(at)] = best
+        if bad is not None:
+            bias[bad] = np.nan
+        w.values["out_bias"] = bias
+        if w.bf16_bits is not None:
+            w.bf16_bits["out_bias"] = (bias.view(np.uint32) >> 16).astype(np.uint16)
+        ctx = pdec.Context(pdec.Model(cfg, w), B, 5, m)
+        ctx.encode(torch.full((B, 5), 9, dtype=torch.int32, device="cuda"), [5] * B)
+        ids, ln, k, fl = [t.cpu().numpy() for t in ctx.decode("jacobi", [m] * B)]
+        assert (ids == at[0]).all() and (ln == m).all() and (k == min(2, m)).all()
+        assert ((fl & pdec.FLAG_NONFINITE != 0) == (bad is not None)).all()
