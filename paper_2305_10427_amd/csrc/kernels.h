@@ -183,6 +183,7 @@ struct LnArgs {
   int d;
   void* out;               // storage type, row-major (nullptr: not written)
   void* feed;              // storage type, MFMA feed order (feed_index; nullptr: not written)
+  int rows_max;            // launch bound on the rows (set by launch_ln)
 };
 
 // One record of the decoding trace: the token an iteration produced at a
