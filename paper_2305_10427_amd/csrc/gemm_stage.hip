@@ -1,10 +1,10 @@
 // The vocabulary projection of many rows (batched sentences times block
-// positions, teacher-forced rows) on MFMA with both operands staged through LDS
-// by direct loads.
+// positions, teacher-forced rows) and the layers' bf16 products of a thousand
+// rows or more, on MFMA with both operands staged through LDS by direct loads.
 //
-// logit[r][n] = s * (sum_k X[r][k] * W[n][k]) + bias[n], as the fused argmax
-// (EPI_ARGMAX) or stored (EPI_LOGITS).  X and W are in the MFMA feed order, so a
-// stage of one MFMA step is BM / 16 + BN / 16 blocks of 1 KB: each block is one
+// Y[r][n] = sum_k X[r][k] * W[n][k] with the epilogues of k_gemm, the vocabulary
+// as the fused argmax (EPI_ARGMAX) or stored (EPI_LOGITS).  X and W are in the
+// MFMA feed order, so a stage of one MFMA step is BM / 16 + BN / 16 blocks of 1 KB: each block is one
 // wave-wide 16-byte load that lands in LDS without passing through registers,
 // and one conflict-free wave-wide LDS read per use.  A wave owns FM x FN
 // subtiles of 16 x 16.
@@ -24,9 +24,16 @@
 // 252 / 481 / 940 / 1811 us -> 92 / 95 / 154 / 275 / 508 / 913 us (1148 TFLOP/s);
 // logits of 952 / 4160 rows 989 / 4131 -> 715 / 2796 us (4.2 GB stored).
 //
-// Every logit is accumulated from zero in increasing k, as in the streaming
-// vocabulary kernel: a row's values depend neither on the kernel, nor on the
-// tile slot, nor on the other rows of the call.
+// Same arithmetic as the row-streaming kernels, element for element: K is cut
+// into their KR ranges of MFMA steps (one for the vocabulary), a range
+// accumulates from zero in increasing k, range sums are added in range order,
+// and the epilogues evaluate the same expressions.  A row's values depend
+// neither on the kernel, nor on the tile slot, nor on the other rows of the call.
+//
+// Products: 64 x 128 tiles of four 32 x 64 waves (two sets of sums for the
+// ranges leave no room for more at four waves per SIMD), three workgroups per
+// CU.  us against k_gemm_feed: 2048 x 1024 x 4096 (rows, K, N; GELU) 40.9 -> 33.5,
+// 4160 rows 97 -> 62; 4160 x 4096 x 1024 91 -> 64; 4000 x 512 x 2048 27.3 -> 23.6.
 //
 // Tile order for the eight XCDs as in k_gemm_feed (row blocks fastest, eight
 // contiguous chunks).  Rows at or above the device row count are not stored; a
@@ -35,6 +42,7 @@
 #include <cstring>
 
 #include "common.h"
+#include "epilogue.h"
 #include "kernels.h"
 #include "mma.h"
 
@@ -79,8 +87,9 @@ template <int MAX, int LPS> __device__ __forceinline__ void stage_wait_for(int l
 
 }  // namespace
 
-template <typename WT, int EPI, int FM, int FN, int WM, int WN, int NS>
+template <typename WT, int EPI, int FM, int FN, int WM, int WN, int KR, int NS>
 __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_stage(GemmArgs a, int n_rb, int n_tiles) {
+  if constexpr (EPI == EPI_QKV) layer_select(a, blockIdx.y);
   using MM = Mma<WT>;
   using frag = typename MM::frag;
   constexpr int KS = MM::KS;
@@ -108,7 +117,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_stage(GemmArgs a, int 
   const int n = K / KS;                                  // MFMA steps = stages
 
   // the tile's operand blocks: subtiles past the last repeat it (every read lies inside its buffer)
-  const char* wf = static_cast<const char*>(a.wp);
+  const char* wf = static_cast<const char*>(EPI == EPI_QKV && a.n_layers > 1 ? a.w : a.wp);
   const size_t tile_bytes = static_cast<size_t>(16) * K * ES;
   const int rts = min(TA, (R_max + 15) / 16 - m0 / 16), cts = min(TB, (N + 15) / 16 - n0 / 16);
   const i32x4_t xr = buffer_of(static_cast<const char*>(a.x) + (m0 / 16) * tile_bytes,
@@ -143,11 +152,26 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_stage(GemmArgs a, int 
     for (int j = 0; j < FN; ++j) f.b[j] = *reinterpret_cast<const frag*>(pb + buf + j * kBlock);
   };
 
-  floatx4_t acc[FM][FN];
+  floatx4_t acc[FM][FN], tot[KR > 1 ? FM : 1][KR > 1 ? FN : 1];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  // ranges of K: w_cur is the one being accumulated, bnd the first step of the next
+  int w_cur = 0;
+  int bnd = KR > 1 ? n / KR : n + 1;
+  auto fold = [&]() __attribute__((always_inline)) {
+    if constexpr (KR > 1) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          tot[i][j] = w_cur == 0 ? acc[i][j] : tot[i][j] + acc[i][j];
+          acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    ++w_cur;
+  };
 
 #pragma unroll
   for (int s = 0; s < NS; ++s)
@@ -155,6 +179,14 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_stage(GemmArgs a, int 
   stage_wait_for<NS - 1, LPS>(n - 1);
   read(f0, 0);
   uint32_t cur = 0;                                      // LDS offset of stage s
+  auto range_edge = [&](int s) __attribute__((always_inline)) {
+    if constexpr (KR > 1) {
+      while (w_cur + 1 < KR && s == bnd) {
+        fold();
+        bnd = (n * (w_cur + 1)) / KR;
+      }
+    }
+  };
   auto step_row = [&](const Frags& f, int i) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = MM::step(f.a[i], f.b[j], acc[i][j]);
@@ -164,6 +196,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_stage(GemmArgs a, int 
   // in order: all of them up front leave its matrix unit idle meanwhile).
   auto iter = [&](int s, const Frags& f, Frags& fn) __attribute__((always_inline)) {
     const uint32_t nxt = cur == (NS - 1) * STAGE ? 0 : cur + STAGE;
+    range_edge(s);
     stage_wait<(NS - 2) * LPS>();                        // stage s + 1 has landed, every wave has read stage s
     const uint32_t at = lds0 + cur + wave * kBlock, ks = static_cast<uint32_t>(s + NS) * kBlock;
 #pragma unroll
@@ -185,6 +218,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_stage(GemmArgs a, int 
   };
   auto last = [&](int s, const Frags& f, Frags& fn) __attribute__((always_inline)) {
     const uint32_t nxt = cur == (NS - 1) * STAGE ? 0 : cur + STAGE;
+    range_edge(s);
     if (s + 1 < n) {
       stage_wait_for<NS - 2, LPS>(n - 2 - s);
       if (s + NS < n) issue(s + NS, cur);
@@ -204,6 +238,12 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_stage(GemmArgs a, int 
     last(s0 + 1, f1, f0);
   }
   if (s0 < n) last(s0, f0, f1);
+  if constexpr (KR > 1)
+    while (w_cur < KR) fold();                           // the last range, then any empty trailing ranges
+  auto res = [&](int i, int j) __attribute__((always_inline)) -> const floatx4_t& {
+    if constexpr (KR > 1) return tot[i][j];
+    else return acc[i][j];
+  };
   __syncthreads();                                       // the stages are dead: LDS holds outputs from here
 
   if constexpr (EPI == EPI_ARGMAX) {
@@ -232,7 +272,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_stage(GemmArgs a, int 
         if (whole) {
 #pragma unroll
           for (int j = 0; j < FN; ++j) {
-            const float logit = fmaf(a.logit_scale, acc[i][j][e], bias_v[j]);   // s * (h . E[col]) + bias[col]
+            const float logit = fmaf(a.logit_scale, res(i, j)[e], bias_v[j]);   // s * (h . E[col]) + bias[col]
             chk = fmaf(logit, 0.f, chk);                 // NaN once a logit is not finite
             const bool t = logit > best;
             best = t ? logit : best;
@@ -252,7 +292,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_stage(GemmArgs a, int 
 #pragma unroll
           for (int j = 0; j < FN; ++j) {
             const uint32_t col = c0 + 16u * j;
-            const float logit = fmaf(a.logit_scale, acc[i][j][e], bias_v[j]);
+            const float logit = fmaf(a.logit_scale, res(i, j)[e], bias_v[j]);
             if (col < static_cast<uint32_t>(N)) {
               if (!isfinite(logit)) nf = 1u;
               else {
@@ -300,7 +340,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_stage(GemmArgs a, int 
 #pragma unroll
       for (int j = 0; j < FN; ++j)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) part[(4 * lg + e) * LD + 16 * j + lr] = acc[i][j][e];
+        for (int e = 0; e < 4; ++e) part[(4 * lg + e) * LD + 16 * j + lr] = res(i, j)[e];
       wave_lds_sync();
     };
     if constexpr (EPI == EPI_LOGITS) {
@@ -321,6 +361,47 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_stage(GemmArgs a, int 
         }
         wave_lds_sync();                                 // the next subtile overwrites the slice
       }
+    } else {
+      // a lane finishes eight columns of PASS rows of each subtile; what it
+      // reads for them from memory is requested first, for all of its rows
+      constexpr int GR = 2 * FN, RP = kWave / GR, PASS = 16 / RP, RW = EPI == EPI_RESID ? ES / 2 : 0;
+      const int tr0 = lane / GR, cl = lane % GR * 8, col = nw + cl;
+      const int col_ok = min(col, N - 8);
+      float bias8[8];
+      load_n<WT, 8>(static_cast<const WT*>(a.bias), col_ok, bias8);
+      u32x4_t rw[FM * PASS][RW > 0 ? RW : 1];
+      int sent[EPI == EPI_QKV ? FM * PASS : 1], pos[EPI == EPI_QKV ? FM * PASS : 1];
+      if constexpr (EPI == EPI_RESID || EPI == EPI_QKV) {
+#pragma unroll
+        for (int t = 0; t < FM * PASS; ++t) {
+          const int row = min(mw + RP * t + tr0, R - 1);
+          if constexpr (EPI == EPI_QKV) row_place(a.rows, row, sent[t], pos[t]);
+#pragma unroll
+          for (int x = 0; x < RW; ++x)
+            rw[t][x] = reinterpret_cast<const u32x4_t*>(static_cast<const WT*>(a.resid) + static_cast<size_t>(row) * a.ldr + col_ok)[x];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        if (mw + 16 * i >= R) break;                     // wave-uniform
+        to_lds(i);
+#pragma unroll
+        for (int u = 0; u < PASS; ++u) {
+          const int t = i * PASS + u, tr = u * RP + tr0, row = mw + 16 * i + tr;
+          float v[8], rv[8];
+          *reinterpret_cast<floatx4_t*>(v) = *reinterpret_cast<const floatx4_t*>(part + tr * LD + cl);
+          *reinterpret_cast<floatx4_t*>(v + 4) = *reinterpret_cast<const floatx4_t*>(part + tr * LD + cl + 4);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            if constexpr (RW == 1) rv[e] = __uint_as_float((e & 1) ? (rw[t][0][e >> 1] & 0xffff0000u) : (rw[t][0][e >> 1] << 16));
+            else if constexpr (RW == 2) rv[e] = __uint_as_float(rw[t][e >> 2][e & 3]);
+            else rv[e] = 0.f;
+          }
+          if (row < R && col < N)
+            finish8<WT, EPI>(a, row, col, v, bias8, rv, EPI == EPI_QKV ? sent[t] : 0, EPI == EPI_QKV ? pos[t] : 0);
+        }
+        wave_lds_sync();                                 // the next subtile overwrites the slice
+      }
     }
   }
 }
@@ -328,9 +409,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_stage(GemmArgs a, int 
 namespace {
 
 // Tiles (rows x columns of a workgroup) and ring depths.
-enum StageCfg { S_NONE = -1, S_64x256 = 0, S_128x128, S_128x256, S_256x256, S_COUNT };
+enum StageCfg { S_NONE = -1, S_64x256 = 0, S_128x128, S_128x256, S_256x256, S_COUNT };   // vocabulary; products: 64 x 128
 
-template <typename WT, int EPI, int FM, int FN, int WM, int WN, int NS>
+template <typename WT, int EPI, int FM, int FN, int WM, int WN, int KR, int NS>
 hipError_t launch_shape(const GemmArgs& a, hipStream_t s, bool init) {
   constexpr int BM = 16 * FM * WM, BN = 16 * FN * WN, NW = WM * WN;
   constexpr size_t stages = static_cast<size_t>(NS) * (BM + BN) / 16 * kBlock;
@@ -339,29 +420,48 @@ hipError_t launch_shape(const GemmArgs& a, hipStream_t s, bool init) {
   static_assert(lds <= 160 * 1024, "LDS of a CU");
   const int n_rb = (a.n_rows + BM - 1) / BM;
   const int n_tiles = n_rb * ((a.N + BN - 1) / BN);
-  auto kernel = &k_gemm_stage<WT, EPI, FM, FN, WM, WN, NS>;
+  const int gy = EPI == EPI_QKV && a.n_layers > 1 ? a.n_layers : 1;
+  auto kernel = &k_gemm_stage<WT, EPI, FM, FN, WM, WN, KR, NS>;
   if (init) {          // gfx950 has 160 KB of LDS per CU
     if (lds <= 65536) return hipSuccess;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                static_cast<int>(lds));
   }
-  hipLaunchKernelGGL(kernel, dim3(n_tiles), dim3(64 * NW), lds, s, a, n_rb, n_tiles);
+  hipLaunchKernelGGL(kernel, dim3(n_tiles, gy), dim3(64 * NW), lds, s, a, n_rb, n_tiles);
   return hipGetLastError();
 }
 
 template <typename WT, int EPI> hipError_t launch_cfg(const GemmArgs& a, int cfg, hipStream_t s, bool init) {
-  if (cfg == S_128x256) return launch_shape<WT, EPI, 4, 8, 2, 2, 3>(a, s, init);
+  if (cfg == S_128x256) return launch_shape<WT, EPI, 4, 8, 2, 2, 1, 3>(a, s, init);
   if constexpr (std::is_same<WT, bf16_t>::value) {
-    if (cfg == S_64x256) return launch_shape<WT, EPI, 4, 4, 1, 4, 4>(a, s, init);
-    if (cfg == S_128x128) return launch_shape<WT, EPI, 4, 4, 2, 2, 3>(a, s, init);
+    if (cfg == S_64x256) return launch_shape<WT, EPI, 4, 4, 1, 4, 1, 4>(a, s, init);
+    if (cfg == S_128x128) return launch_shape<WT, EPI, 4, 4, 2, 2, 1, 3>(a, s, init);
     if constexpr (EPI == EPI_LOGITS)
-      if (cfg == S_256x256) return launch_shape<WT, EPI, 8, 4, 2, 4, 4>(a, s, init);
+      if (cfg == S_256x256) return launch_shape<WT, EPI, 8, 4, 2, 4, 1, 4>(a, s, init);
   }
   return init ? hipSuccess : hipErrorInvalidValue;
 }
 
 template <typename WT> hipError_t launch_w(int epi, int cfg, const GemmArgs& a, hipStream_t s, bool init) {
   return epi == EPI_ARGMAX ? launch_cfg<WT, EPI_ARGMAX>(a, cfg, s, init) : launch_cfg<WT, EPI_LOGITS>(a, cfg, s, init);
+}
+
+template <int EPI> hipError_t launch_product(const GemmArgs& a, int ksplit, hipStream_t s) {   // 48 KB of LDS
+  return ksplit == 8 ? launch_shape<bf16_t, EPI, 2, 4, 2, 2, 8, 4>(a, s, false)
+                     : launch_shape<bf16_t, EPI, 2, 4, 2, 2, 4, 4>(a, s, false);
+}
+
+// Whether a bf16 product in feed order runs on 64 x 128 staged tiles: enough
+// of them for the workgroups of a CU to cover each other's fixed parts (about
+// 5 us a tile at 1.4 of them per CU), sooner where K is long.  us, k_gemm_feed
+// against staged, by tiles: K = 1024: 256 tiles 11.2 / 11.6, 376 19.8 / 15.4, 480
+// (GELU) 21.1 / 18.8, 576 22.2 / 19.7, 2112 97 / 62; K = 512: 256 8.8 / 10.8, 384
+// 11.0 / 10.9, 512 14.5 / 13.4; K = 4096: 120 23.1 / 25.6, 192 30.3 / 27.3, 256
+// 41.9 / 28.9; K = 2048: 128 13.1 / 16.6, 252 24.1 / 18.3.
+bool stage_product(int dtype, const GemmArgs& a) {
+  if (dtype != DT_BF16 || !a.x_feed) return false;
+  const long long tiles = static_cast<long long>((a.n_rows + 63) / 64) * ((a.N + 127) / 128) * std::max(a.n_layers, 1);
+  return tiles >= (a.K >= 2048 ? 192 : 360);
 }
 
 // The tile for a vocabulary projection of `rows` rows, S_NONE where k_gemm_feed
@@ -416,6 +516,22 @@ hipError_t launch_vocab_rows(int dtype, int epi, const GemmArgs& a, hipStream_t 
   if (a.K % ks != 0 || a.x_f32 || !a.x_feed || a.wp == nullptr) return hipErrorInvalidValue;
   if (256ull * a.K * es >= (1ull << 31)) return hipErrorInvalidValue;   // byte offsets within a tile fit 31 bits
   return dtype == DT_BF16 ? launch_w<bf16_t>(epi, cfg, a, s, false) : launch_w<float>(epi, cfg, a, s, false);
+}
+
+hipError_t launch_product_rows(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s) {
+  if (a.n_rows <= 0) return hipSuccess;
+  if (!stage_product(dtype, a)) return launch_gemm_feed(dtype, epi, ksplit, a, s);
+  if (a.K % Mma<bf16_t>::KS != 0 || a.x_f32 || ksplit != (a.K >= 2048 ? 8 : 4) || a.N % 16 != 0) return hipErrorInvalidValue;
+  if (256ull * a.K * sizeof(bf16_t) >= (1ull << 31)) return hipErrorInvalidValue;
+  if (a.out_feed && (epi != EPI_ACT || a.N % 32 != 0)) return hipErrorInvalidValue;
+  if (!(epi == EPI_QKV && a.n_layers > 1) && a.wp == nullptr) return hipErrorInvalidValue;
+  switch (epi) {
+    case EPI_F32: return launch_product<EPI_F32>(a, ksplit, s);
+    case EPI_ACT: return launch_product<EPI_ACT>(a, ksplit, s);
+    case EPI_RESID: return launch_product<EPI_RESID>(a, ksplit, s);
+    case EPI_QKV: return launch_product<EPI_QKV>(a, ksplit, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace pdec

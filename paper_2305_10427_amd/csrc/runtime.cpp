@@ -316,7 +316,7 @@ hipError_t run_gemm(pd_ctx& C, const Rows& r, GemmArgs g, int epi, bool pro_ln, 
   }
   if (vocab) return launch_vocab_rows(M.dt, epi, g, s);
   const int ksplit = epi == EPI_LOGITS ? 1 : (g.K >= 2048 ? 8 : 4);
-  if (many) return launch_gemm_feed(M.dt, epi, ksplit, g, s);
+  if (many) return launch_product_rows(M.dt, epi, ksplit, g, s);
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   if (C.gemm_slot >= 0) {   // a timed decoder product: the next event pair of the slot, and its bytes
     const int sl = C.gemm_slot;

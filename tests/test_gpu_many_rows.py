@@ -114,3 +114,9 @@ def test_argmax_of_planted_logits(dtype, d, heads, B, m):
         ids, ln, k, fl = [t.cpu().numpy() for t in ctx.decode("jacobi", [m] * B)]
         assert (ids == at[0]).all() and (ln == m).all() and (k == min(2, m)).all()
         assert ((fl & pdec.FLAG_NONFINITE != 0) == (bad is not None)).all()
+
+
+@pytest.mark.parametrize("d,heads,d_ff,B,T", [(512, 8, 2048, 48, 65), (544, 17, 2080, 50, 63)])
+def test_staged_products_are_bitwise_those_of_few_rows(d, heads, d_ff, B, T):
+    """Enough rows for every layer product to run on staged tiles: ragged row and column tiles, K of four and eight ranges."""
+    compare(dataclasses.replace(cfg_of("bf16", d, heads, d_ff), n_dec=1), B, 64, T)
