@@ -378,14 +378,13 @@ hipError_t decoder_pass(pd_ctx& C, const Rows& r, float* logits, hipStream_t s, 
     SlotScope(pd_ctx& c_, int sl) : c(c_) { c.gemm_slot = sl; }
     ~SlotScope() { c.gemm_slot = -1; }
   } scope(C, logits == nullptr ? slot : -1);
-  // iterations of 9..16 rows pass the attention output and the FFN hidden
-  // layer in the MFMA feed order (the products that read them then load 1 KB
-  // contiguous per step instead of 64 bytes from each of 16 rows; with fewer
-  // rows the row-major loads, which repeat rows, cost about the same or less:
-  // large model, 16 rows: 650.6 -> 616.9 us per iteration; MT-base, 5 rows:
-  // 204.5 -> 206.4)
-  // iterations of many rows pass them in that order too
-  const int feed = (r.R_max > 8 && r.R_max <= 16) || many_rows(M, r.R_max) ? 1 : 0;
+  // iterations of more than 8 rows pass the attention output and the FFN
+  // hidden layer in the MFMA feed order (the products that read them then load
+  // 1 KB contiguous per step instead of 64 bytes from each of 16 rows; with
+  // fewer rows the row-major loads, which repeat rows, cost about the same or
+  // less: large model, 16 rows: 650.6 -> 616.9 us per iteration; MT-base, 5
+  // rows: 204.5 -> 206.4)
+  const int feed = r.R_max > 8 ? 1 : 0;
   for (int l = 0; l < cfg.n_dec; ++l) {
     // self-attention: Q -> q_buf, K/V of the block -> cache (layer l)
     GemmArgs g = gemm_base(r);
@@ -516,7 +515,7 @@ hipError_t encoder_pass(pd_ctx& C, const int32_t* src, int B, int n_max, const i
   const size_t es = M.dt == DT_BF16 ? 2 : 4;
   const size_t cross_layer = static_cast<size_t>(C.max_batch) * C.max_src * d * es;
   const int R = B * n_max;
-  const int feed = many_rows(M, R) ? 1 : 0;   // activations between the kernels in feed order
+  const int feed = R > 8 ? 1 : 0;   // activations between the kernels in feed order, as in the decoder
   Rows r{nullptr, R, RowMap{nullptr, nullptr, n_max}, src, R};
   const int* klen = C.at<int>(C.L.src_len);
   const float scale = 1.0f / std::sqrt(static_cast<float>(M.dh));
@@ -590,14 +589,14 @@ hipError_t encoder_pass(pd_ctx& C, const int32_t* src, int B, int n_max, const i
     if (pre) { g.x = x_res; g.x_f32 = 0; g.ln_g = M.enc_ln(0); g.ln_b = M.enc_ln(1); }
     else { g.x = s_buf; g.x_f32 = 1; g.ln_g = M.enc(cfg.n_enc - 1, E_LN2G); g.ln_b = M.enc(cfg.n_enc - 1, E_LN2B); }
     g.ln_eps = cfg.ln_eps;
-    g.ldx = d; g.w = M.dec(l0, D_CWKV); g.wp = feed ? M.dec_feed(l0, D_CWKV) : nullptr; g.bias = M.dec(l0, D_CBKV); g.N = 2 * d; g.K = d;
+    g.ldx = d; g.w = M.dec(l0, D_CWKV); g.wp = many_rows(M, R) ? M.dec_feed(l0, D_CWKV) : nullptr; g.bias = M.dec(l0, D_CBKV); g.N = 2 * d; g.K = d;
     g.q_cols = 0;
     g.kc = C.at<char>(C.L.cross_k) + l0 * cross_layer; g.vc = C.at<char>(C.L.cross_v) + l0 * cross_layer;
     g.H = M.H; g.dh = M.dh; g.T = C.max_src; g.d = d;
     g.n_layers = nl;
     g.kv_stride = static_cast<long long>(cross_layer);
     for (int z = 0; z < nl; ++z) {
-      g.lw[z] = feed ? M.dec_feed(l0 + z, D_CWKV) : M.dec(l0 + z, D_CWKV);
+      g.lw[z] = many_rows(M, R) ? M.dec_feed(l0 + z, D_CWKV) : M.dec(l0 + z, D_CWKV);
       g.lb[z] = M.dec(l0 + z, D_CBKV);
     }
     if ((e = run_gemm(C, r, g, EPI_QKV, true, a_buf, s)) != hipSuccess) return e;
