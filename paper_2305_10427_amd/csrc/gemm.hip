@@ -50,9 +50,6 @@
 // ln_stats16) and rounds them to the storage type before use; workgroup 0
 // can write the normalised rows out as the new residual stream.
 //
-// Epilogue EPI_ARGMAX is the fused vocabulary projection + argmax: logits =
-// s * acc + bias are never stored; each workgroup keeps the best (largest
-// value, then lowest index) per row and writes one partial per row.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -65,7 +62,7 @@ namespace pdec {
 
 constexpr int kDepth = 8;   // MFMA steps per weight batch; two batches are in flight
 
-template <typename WT, int PRO, int EPI, int XF32, int KSPLIT, int LNT, int RG, int SPW>
+template <typename WT, int PRO, int EPI, int XF32, int KSPLIT, int LNT, int RG, int SPW, int ONE = 0>
 __global__ __launch_bounds__(KSPLIT == 8 ? 512 : 256) void k_gemm(GemmArgs a) {
   if constexpr (EPI == EPI_QKV) layer_select(a, blockIdx.z);
   using AT = WT;
@@ -83,6 +80,7 @@ __global__ __launch_bounds__(KSPLIT == 8 ? 512 : 256) void k_gemm(GemmArgs a) {
   constexpr bool SPLIT = KSPLIT > 1;   // waves split K over one 16-column tile
   static_assert(RG == 16 || (SPLIT && (RG == 4 || RG == 8)), "row groups of 4 or 8 rows need the K split");
   static_assert(SPW == 0 || SPLIT, "whole-range loads need the K split");
+  static_assert(ONE == 0 || (SPW > 0 && PRO == PRO_NONE && RG == 16), "one row through LDS");
   int ctile = blockIdx.x, grp = 0;     // column tile and row group of this workgroup
   if constexpr (RG < 16) {
     const int ct = (N + 15) / 16;
@@ -152,6 +150,15 @@ __global__ __launch_bounds__(KSPLIT == 8 ? 512 : 256) void k_gemm(GemmArgs a) {
       row_place(a.rows, row < R_max ? row : 0, rs[e], rp[e]);
     }
   }
+  // ONE (launches of one row): this wave's slice of the row, 16 bytes a lane
+  // (lanes past the slice repeat it), instead of a load per step whose 16-lane
+  // groups all read the same bytes: those cost the cache's address path as much
+  // as the weights do
+  constexpr int kRowWords = SPW > 0 ? 4 * SPW : 1;
+  __shared__ uint4 s_x[ONE ? KSPLIT : 1][ONE ? kRowWords : 1];
+  uint4 xw = make_uint4(0u, 0u, 0u, 0u);
+  if constexpr (ONE != 0)
+    xw = *reinterpret_cast<const uint4*>(X + s_begin * KS + lane % kRowWords * EPL);
   __builtin_amdgcn_sched_barrier(0);   // keep the loads above ahead of the weights
 
   // the first weight batch
@@ -162,9 +169,6 @@ __global__ __launch_bounds__(KSPLIT == 8 ? 512 : 256) void k_gemm(GemmArgs a) {
   const int R = a.n_rows_dev ? *a.n_rows_dev : a.n_rows;
 
   __shared__ float s_part[KSPLIT > 1 ? KSPLIT : 1][4][64];
-  __shared__ uint32_t s_key[4][16];
-  __shared__ int s_idx[4][16];
-  __shared__ float2 s_lse[EPI == EPI_ARGMAX ? 4 : 1][16];
   // PRO_LN: the normalised 16-row input tile, rows padded by 16 bytes
   extern __shared__ __align__(16) unsigned char s_dyn[];
   AT* sA = reinterpret_cast<AT*>(s_dyn);
@@ -210,8 +214,15 @@ __global__ __launch_bounds__(KSPLIT == 8 ? 512 : 256) void k_gemm(GemmArgs a) {
     if constexpr (SPW > 0) {
       // the whole range: bcur holds its SPW weight steps
       frag af[D];
+      if constexpr (ONE != 0) {
+        s_x[wave][lane % kRowWords] = xw;
+        wave_lds_sync();
 #pragma unroll
-      for (int u = 0; u < D; ++u) af[u] = a_frag(s_begin + u);
+        for (int u = 0; u < D; ++u) af[u] = __builtin_bit_cast(frag, s_x[wave][4 * u + lg]);
+      } else {
+#pragma unroll
+        for (int u = 0; u < D; ++u) af[u] = a_frag(s_begin + u);
+      }
 #pragma unroll
       for (int u = 0; u < D; ++u) acc = MM::step(af[u], bcur[u], acc);
     } else
@@ -254,10 +265,6 @@ __global__ __launch_bounds__(KSPLIT == 8 ? 512 : 256) void k_gemm(GemmArgs a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) cv[i] = acc[i];
     }
-    uint32_t bk[4] = {0u, 0u, 0u, 0u};
-    uint32_t bi[4] = {0x7fffffffu, 0x7fffffffu, 0x7fffffffu, 0x7fffffffu};
-    uint32_t nf = 0;
-    float lm[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY}, ls[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
       const int i = SPLIT ? wave : e;
@@ -294,59 +301,7 @@ __global__ __launch_bounds__(KSPLIT == 8 ? 512 : 256) void k_gemm(GemmArgs a) {
         }
       } else if constexpr (EPI == EPI_LOGITS) {
         a.out_f32[static_cast<size_t>(row) * a.ldo + col] = fmaf(a.logit_scale, v, bias_v);
-      } else if constexpr (EPI == EPI_ARGMAX) {
-        const float logit = fmaf(a.logit_scale, v, bias_v);   // s * (h . E[col]) + bias[col]
-        if (!isfinite(logit)) nf |= 1u << e;   // bit e: a non-finite logit in row 4 lg + e
-        else {
-          bk[e] = float_key(logit);
-          bi[e] = static_cast<uint32_t>(col);
-          lm[e] = logit;
-          ls[e] = 1.f;
-        }
       }
-    }
-    if constexpr (EPI == EPI_ARGMAX) {
-      static_assert(KSPLIT == 1, "the fused argmax runs with whole-K waves");
-      // best of each row over the 16 columns held by one 16-lane group
-#pragma unroll
-      for (int e = 0; e < 4; ++e) group16_best(bk[e], bi[e]);
-      nf = group16_or(nf);
-      const bool want_lse = a.part_lse != nullptr;
-      if (want_lse) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) group16_lse(lm[e], ls[e]);
-      }
-      if (lr == 0) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          s_key[wave][4 * lg + e] = bk[e];
-          s_idx[wave][4 * lg + e] = static_cast<int>(bi[e] | (((nf >> e) & 1u) << 31));
-          if (want_lse) s_lse[wave][4 * lg + e] = make_float2(lm[e], ls[e]);
-        }
-      }
-      __syncthreads();
-      if (threadIdx.x < 16) {
-        const int r = threadIdx.x;
-        uint32_t kk = 0;
-        int ii = 0x7fffffff, ff = 0;
-        for (int w = 0; w < 4; ++w) {
-          const uint32_t k2 = s_key[w][r];
-          const int raw = s_idx[w][r];
-          const int i2 = raw & 0x7fffffff;
-          ff |= (raw >> 31) & 1;
-          if (k2 > kk || (k2 == kk && i2 < ii)) { kk = k2; ii = i2; }
-        }
-        if (m0 + r < R) {
-          a.partials[static_cast<size_t>(m0 + r) * a.part_ld + blockIdx.x] =
-              make_uint2(kk, static_cast<uint32_t>(ii) | (static_cast<uint32_t>(ff) << 31));
-          if (want_lse) {
-            float m = s_lse[0][r].x, sm = s_lse[0][r].y;
-            for (int w = 1; w < 4; ++w) lse_merge(m, sm, s_lse[w][r].x, s_lse[w][r].y);   // wave order
-            a.part_lse[static_cast<size_t>(m0 + r) * a.part_ld + blockIdx.x] = make_float2(m, sm);
-          }
-        }
-      }
-      __syncthreads();
     }
   }
 }
@@ -378,6 +333,18 @@ int row_group(int pro, int col_tiles, int rows, int layers) {
 template <typename WT, int PRO, int EPI, int XF32, int LNT, int KSPLIT, int RG>
 void launch_rg(const GemmArgs& a, int spw, dim3 grid, size_t lds, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   constexpr int NT = KSPLIT == 8 ? 512 : 256;
+  // One row (a greedy step of one sentence): through LDS.  Large model, greedy
+  // step with 36 such products 472 -> 456 us, MT-base 184 -> 182; at 5 rows the
+  // same through LDS was slower (float32 MT-base iteration 242 -> 255 us).
+  if constexpr (PRO == PRO_NONE && EPI == EPI_RESID && RG == 16) {
+    if (a.n_rows == 1 && !a.x_feed) {
+      if constexpr (KSPLIT == 8)
+        if (spw == 16) return launch_ev(k_gemm<WT, PRO, EPI, XF32, 8, LNT, RG, 16, 1>, grid, dim3(NT), lds, s, ev0, ev1, a);
+      if (spw == 8) return launch_ev(k_gemm<WT, PRO, EPI, XF32, KSPLIT, LNT, RG, 8, 1>, grid, dim3(NT), lds, s, ev0, ev1, a);
+      if constexpr (KSPLIT == 4)
+        if (spw == 4) return launch_ev(k_gemm<WT, PRO, EPI, XF32, 4, LNT, RG, 4, 1>, grid, dim3(NT), lds, s, ev0, ev1, a);
+    }
+  }
   if constexpr (KSPLIT == 8) {
     if (spw == 16) return launch_ev(k_gemm<WT, PRO, EPI, XF32, 8, LNT, RG, 16>, grid, dim3(NT), lds, s, ev0, ev1, a);
     if (spw == 8) return launch_ev(k_gemm<WT, PRO, EPI, XF32, 8, LNT, RG, 8>, grid, dim3(NT), lds, s, ev0, ev1, a);
@@ -409,11 +376,11 @@ hipError_t launch_k(GemmArgs a, int ksplit, hipStream_t s, hipEvent_t ev0, hipEv
   const size_t lds = PRO == PRO_LN ? gemm_ln_lds_bytes(a.K, sizeof(WT)) : 0;
   const int gz = EPI == EPI_QKV && a.n_layers > 1 ? a.n_layers : 1;
   if (gz > 1 || a.N % 16 != 0) a.wp = nullptr;   // the packed copy covers single-layer products with whole tiles
-  if (EPI == EPI_ARGMAX || ksplit == 1) {
+  if constexpr (EPI == EPI_LOGITS) {   // whole-K waves
     a.wp = nullptr;
     launch_ev(k_gemm<WT, PRO, EPI, XF32, 1, LNT, 16, 0>, dim3(gemm_grid(EPI, a.N, 1), gy, gz), dim3(256), lds, s, ev0,
               ev1, a);
-  } else if constexpr (EPI != EPI_ARGMAX) {
+  } else {
     if (ksplit == 8) launch_split<WT, PRO, EPI, XF32, LNT, 8>(a, gy, gz, lds, s, ev0, ev1);
     else launch_split<WT, PRO, EPI, XF32, LNT, 4>(a, gy, gz, lds, s, ev0, ev1);
   }
@@ -436,7 +403,6 @@ hipError_t launch_epi(int epi, const GemmArgs& a, int ksplit, hipStream_t s, hip
     case EPI_ACT: return launch_t<WT, PRO, EPI_ACT, XF32>(a, ksplit, s, ev0, ev1);
     case EPI_RESID: return launch_t<WT, PRO, EPI_RESID, XF32>(a, ksplit, s, ev0, ev1);
     case EPI_QKV: return launch_t<WT, PRO, EPI_QKV, XF32>(a, ksplit, s, ev0, ev1);
-    case EPI_ARGMAX: return launch_t<WT, PRO, EPI_ARGMAX, XF32>(a, ksplit, s, ev0, ev1);
     case EPI_LOGITS: return launch_t<WT, PRO, EPI_LOGITS, XF32>(a, ksplit, s, ev0, ev1);
     default: return hipErrorInvalidValue;
   }
@@ -497,6 +463,7 @@ hipError_t launch_pack_feed(int dtype, const void* w, void* out, int N, int K, h
 hipError_t launch_gemm(int dtype, int pro, int epi, int ksplit, const GemmArgs& a, hipStream_t s, hipEvent_t ev0,
                        hipEvent_t ev1) {
   if (a.n_rows <= 0) return hipSuccess;
+  if ((epi == EPI_LOGITS) != (ksplit == 1)) return hipErrorInvalidValue;
   if (a.x_feed && (pro == PRO_LN || a.x_f32 || ksplit == 1)) return hipErrorInvalidValue;
   if (a.out_feed && (epi != EPI_ACT || ksplit == 1 || a.N % 32 != 0)) return hipErrorInvalidValue;
   const int ks = dtype == DT_BF16 ? Mma<bf16_t>::KS : Mma<float>::KS;

@@ -120,3 +120,21 @@ def test_argmax_of_planted_logits(dtype, d, heads, B, m):
 def test_staged_products_are_bitwise_those_of_few_rows(d, heads, d_ff, B, T):
     """Enough rows for every layer product to run on staged tiles: ragged row and column tiles, K of four and eight ranges."""
     compare(dataclasses.replace(cfg_of("bf16", d, heads, d_ff), n_dec=1), B, 64, T)
+
+
+@pytest.mark.parametrize("dtype,d,heads,d_ff", [("bf16", 256, 4, 2048), ("f32", 128, 4, 4096), ("bf16", 128, 2, 512),
+                                                ("f32", 256, 4, 1024), ("bf16", 1024, 16, 4096)])
+@pytest.mark.parametrize("T", [1, 2, 7, 8, 9, 16])
+def test_few_rows_are_bitwise_those_of_a_longer_call(dtype, d, heads, d_ff, T):
+    """Launches of 1 to 8 rows (input rows through LDS) and of 9 and more (feed order), each whole K range in flight."""
+    compare_prefix(cfg_of(dtype, d, heads, d_ff), T)
+
+
+def compare_prefix(cfg, T):
+    gm = pdec.Model(cfg, synth.make_weights(cfg, seed=7, bias_std=0.3, ln_std=0.2))
+    g = np.random.default_rng(T)
+    src = g.integers(4, cfg.vocab, (1, 5)).astype(np.int32)
+    tgt = g.integers(4, cfg.vocab, (1, 40)).astype(np.int32)
+    ctx = pdec.Context(gm, 1, 5, 40)
+    want = logits(ctx, src, [5], tgt)
+    np.testing.assert_array_equal(logits(ctx, src, [5], tgt[:, :T]), want[:, :T])
