@@ -316,10 +316,18 @@ hipError_t gemm_feed_init() {
   return hipSuccess;
 }
 
-static int gemm_feed_cfg(int N, int rows) {
+// The largest tile that still gives `least` workgroups: a larger one reads less
+// through the cache, a smaller one leaves fewer CUs with an extra tile.
+// bf16, bound by the cache: 192 of them, measured against 256 / 512: batch-8
+// scoring of the large model 3391 against 3466 / 3712 us, MT-base batch 16 1192
+// against 1245 / 1267 (160 and 224 as 192).  float32, bound by the matrix units, so
+// an even spread counts: 1024, against 256 / 512: MT-base batch-16 scoring 1974
+// against 2113 / 2025 us, batch 4 1086 / 1108 / 1087, batch 40 6472 / 6577 / 6602.
+static int gemm_feed_cfg(int dtype, int N, int rows) {
   const auto wgs = [&](int bm, int bn) { return ((rows + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  if (wgs(64, 64) >= 256) return P_64x64;
-  if (wgs(32, 64) >= 256) return P_32x64;
+  const int least = dtype == DT_BF16 ? 192 : 1024;
+  if (wgs(64, 64) >= least) return P_64x64;
+  if (wgs(32, 64) >= least) return P_32x64;
   return P_32x32;
 }
 
@@ -333,7 +341,7 @@ hipError_t launch_gemm_feed(int dtype, int epi, int ksplit, const GemmArgs& a, h
   if (256ull * std::max(a.ldx, a.K) * es >= (1ull << 31)) return hipErrorInvalidValue;
   if (a.out_feed && (epi != EPI_ACT || a.N % 32 != 0)) return hipErrorInvalidValue;
   if (!(epi == EPI_QKV && a.n_layers > 1) && a.wp == nullptr) return hipErrorInvalidValue;
-  const int cfg = gemm_feed_cfg(a.N, a.n_rows);
+  const int cfg = gemm_feed_cfg(dtype, a.N, a.n_rows);
   return dtype == DT_BF16 ? launch_w<bf16_t>(epi, ksplit, cfg, a, s, false)
                           : launch_w<float>(epi, ksplit, cfg, a, s, false);
 }

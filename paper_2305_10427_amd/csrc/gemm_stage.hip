@@ -67,7 +67,7 @@ __device__ __forceinline__ i32x4_t buffer_of(const char* p, uint32_t n) {
 // written; completion is counted by vmcnt, waited for in stage_wait).
 __device__ __forceinline__ void load_to_lds(i32x4_t r, uint32_t voff, uint32_t soff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory");
+               :: "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory", "m0");
 }
 
 // All but the N youngest loads of this wave have landed and its LDS reads are
