@@ -1227,8 +1227,8 @@ static hipError_t launch_attn_t(const AttnArgs& a, int grid, hipStream_t s) {
 }
 
 template <typename AT>
-static hipError_t launch_attn_tile(const AttnArgs& a, hipStream_t s) {
-  const dim3 grid(a.H, (a.sent_rows + 15) / 16, a.n_sent);
+static hipError_t launch_attn_tile(const AttnArgs& a, int tiles, hipStream_t s) {
+  const dim3 grid(a.H, tiles, a.n_sent);
   switch (a.dh) {
     case 32: hipLaunchKernelGGL((k_attn_tile<AT, 32>), grid, dim3(256), 0, s, a); break;
     case 64: hipLaunchKernelGGL((k_attn_tile<AT, 64>), grid, dim3(256), 0, s, a); break;
@@ -1243,24 +1243,25 @@ static hipError_t launch_attn_tile(const AttnArgs& a, hipStream_t s) {
 // 128 rows 8.8 / 7.9, 64 rows 6.4 / 7.4; 1032 teacher-forced rows 31.8 / 17.0;
 // 53 rows of 8 heads 3.4 / 4.4.  A tile of few rows wastes its products: with
 // blocks of 5 the two are equal.
-bool attn_tiled(int dh, int heads, int sent_rows, int R_max) {
-  return dh >= 32 && sent_rows >= 8 && R_max * heads >= 2048;
+int attn_row_tiles(int dh, int heads, int sent_rows, int R_max) {
+  return dh >= 32 && sent_rows >= 8 && R_max * heads >= 2048 ? (sent_rows + 15) / 16 : 0;
 }
 
 hipError_t launch_attn(int dtype, const AttnArgs& args, int R_max, hipStream_t s) {
   if (args.dh > kMaxHeadDim || args.T > kMaxKeys) return hipErrorInvalidValue;
   if (args.one_source && (args.causal || args.klen == nullptr)) return hipErrorInvalidValue;
   if (!args.causal && args.klen == nullptr) return hipErrorInvalidValue;
-  if (R_max > 0 && attn_tiled(args.dh, args.H, args.sent_rows, R_max)) {
+  const int tiles = R_max > 0 ? attn_row_tiles(args.dh, args.H, args.sent_rows, R_max) : 0;
+  if (tiles > 0) {
     AttnArgs a = args;
     const int per = a.rows.per_sent;
-    if (a.rows.sent == nullptr ? per < 1 || R_max % per != 0 : a.st == nullptr || a.n_sent < 1) return hipErrorInvalidValue;
+    if (a.rows.sent == nullptr ? per != a.sent_rows || R_max % per != 0 : a.st == nullptr || a.n_sent < 1)
+      return hipErrorInvalidValue;
     if (a.rows.sent == nullptr) {        // dense rows: the launch bound is the row count
       a.st = nullptr;
       a.n_sent = R_max / per;
-      a.sent_rows = per;
     }
-    return dtype == DT_BF16 ? launch_attn_tile<bf16_t>(a, s) : launch_attn_tile<float>(a, s);
+    return dtype == DT_BF16 ? launch_attn_tile<bf16_t>(a, tiles, s) : launch_attn_tile<float>(a, tiles, s);
   }
   const int grid = (R_max + kAttnRows - 1) / kAttnRows * args.H;
   if (grid == 0) return hipSuccess;

@@ -312,9 +312,11 @@ hipError_t launch_product_rows(int dtype, int epi, int ksplit, const GemmArgs& a
 hipError_t gemm_stage_init();  // once before the first launch
 int vocab_rows_parts(int dtype, int V, int K, int rows);
 hipError_t launch_vocab_rows(int dtype, int epi, const GemmArgs& a, hipStream_t s);
-// Whether launch_attn evaluates 16 rows of a head together on the matrix cores
-// (bitwise the same rows): sentences of up to sent_rows rows, launch bound R_max.
-bool attn_tiled(int dh, int heads, int sent_rows, int R_max);
+// 16-row tiles per sentence where launch_attn evaluates 16 rows of a head
+// together on the matrix cores (bitwise the same rows), 0 where it goes row by
+// row: sentences of up to sent_rows rows, launch bound R_max.  A captured launch
+// serves sentences of at most that many tiles.
+int attn_row_tiles(int dh, int heads, int sent_rows, int R_max);
 hipError_t launch_attn(int dtype, const AttnArgs& a, int R_max, hipStream_t s);
 // Fused vocabulary projection + argmax for at most 16 rows (streaming kernel);
 // writes vocab_grid(dtype, V, d) partials per row (at most ceil(V / 64)).

@@ -196,16 +196,16 @@ Layout plan(const pd_model& M, int max_batch, int max_src, int max_tgt) {
 struct GraphKey {
   int mode, block, horizon, max_iters, B, R_max, slot, fused;
   int long_keys;   // attention's launch choice: rows of more than one key chunk possible (1 self-attention,
-                   // 2 cross-attention), 4 16-row tiles
+                   // 2 cross-attention)
+  int row_tiles;   // attention's 16-row tiles per sentence (attn_row_tiles; 0: row by row), its grid
   // the trace buffers are kernel arguments of a traced iteration
   const void* trace;
   long long trace_cap;
   const void* trace_part;
   bool operator==(const GraphKey& o) const {
     return mode == o.mode && block == o.block && horizon == o.horizon && max_iters == o.max_iters && B == o.B &&
-           R_max == o.R_max && slot == o.slot && fused == o.fused && long_keys == o.long_keys && trace == o.trace &&
-           trace_cap == o.trace_cap &&
-           trace_part == o.trace_part;
+           R_max == o.R_max && slot == o.slot && fused == o.fused && long_keys == o.long_keys &&
+           row_tiles == o.row_tiles && trace == o.trace && trace_cap == o.trace_cap && trace_part == o.trace_part;
   }
 };
 
@@ -1059,10 +1059,9 @@ pd_status pd_decode_init(pd_ctx* ctx, int32_t mode, int32_t block, int32_t horiz
     if (e == hipSuccess) {
       if (C.use_graphs && slot < 0) {   // iterations timed with events are launched directly
         hipGraphExec_t ex = nullptr;
-        const int long_keys = (C.self_keys > kAttnChunkKeys ? 1 : 0) | (C.src_keys > kAttnChunkKeys ? 2 : 0) |
-                              (attn_tiled(M.dh, M.H, Lmax, Rb) ? 4 : 0);
-        const GraphKey key{key_mode, block, horizon, max_iters, B, Rb, slot, fused ? 1 : 0, long_keys, C.trace,
-                           C.trace_cap, C.trace_part};
+        const int long_keys = (C.self_keys > kAttnChunkKeys ? 1 : 0) | (C.src_keys > kAttnChunkKeys ? 2 : 0);
+        const GraphKey key{key_mode, block, horizon, max_iters, B, Rb, slot, fused ? 1 : 0, long_keys,
+                           attn_row_tiles(M.dh, M.H, C.sent_rows, Rb), C.trace, C.trace_cap, C.trace_part};
         e = iteration_graph(C, key, r, cb, &ex);
         if (e == hipSuccess) e = hipGraphLaunch(ex, s);
       } else {

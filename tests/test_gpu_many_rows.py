@@ -85,6 +85,56 @@ def test_blocks_across_row_tiles_equal_single_decodes(dtype, heads, mode, block)
         np.testing.assert_array_equal(ids[b, :ln[b]], i1[0, :l1[0]])
 
 
+def launch_bound(rows, full):
+    """Rows an iteration of `rows` rows is launched (and its graph captured) for."""
+    b = 1
+    while b < min(rows, full):
+        b *= 2
+    return min(b, full)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("mode,block,short,long", [("jacobi", 1, [40] + [20] * 7, [60] + [20] * 7),
+                                                   ("jacobi", 1, [70] + [30] * 15, [100] + [30] * 15),
+                                                   ("gs_jacobi", 32, [16] + [14] * 15, [32] + [14] * 15),
+                                                   ("hybrid", 32, [16] + [14] * 15, [64] + [14] * 15)])
+def test_a_context_decodes_longer_targets_after_shorter_ones(monkeypatch, dtype, mode, block, short, long):
+    """A graph captured for short blocks (16-row attention tiles of 8 heads) must not serve longer blocks of the
+    same launch bound: what a context decodes, and its trace (whose logits show rows that the argmax hides), equal
+    a fresh context's, with graphs and without."""
+    import torch
+    cfg = cfg_of(dtype, 256, 8, 512, pre_ln=False)
+    gm = pdec.Model(cfg, synth.make_weights(cfg, seed=6, eos_bias=-128.0))     # whole targets, dozens of iterations
+    B, n = len(short), 20
+    rows = [[min(x, block if mode != "jacobi" else x) for x in ms] for ms in (short, long)]
+    bounds = [launch_bound(sum(r), B * max(r)) for r in rows]
+    assert bounds[0] == bounds[1] and bounds[0] * cfg.n_heads >= 2048
+    src = torch.from_numpy(np.random.default_rng(3).integers(4, cfg.vocab, (B, n)).astype(np.int32)).cuda()
+
+    def context():
+        c = pdec.Context(gm, B, n, 100)
+        c.encode(src, [n] * B)
+        c.set_trace(200000, B * 100)
+        return c
+
+    def decode(c, ms):
+        before = c.trace()[1]
+        out = [t.cpu().numpy() for t in c.decode(mode, ms, block=block)]
+        torch.cuda.synchronize()
+        return out + [c.trace()[0][before:]]
+
+    kept = context()
+    for ms in (short, long, short):
+        got, fresh = decode(kept, ms), decode(context(), ms)
+        monkeypatch.setenv("PDEC_GRAPHS", "0")
+        direct = decode(context(), ms)
+        monkeypatch.delenv("PDEC_GRAPHS")
+        assert direct[2].max() >= 16 and len(direct[4]) < 60000
+        for g, f, w in zip(got, fresh, direct):
+            np.testing.assert_array_equal(g, w)
+            np.testing.assert_array_equal(f, w)
+
+
 @pytest.mark.parametrize("dtype,d,heads,vocab", [("bf16", 640, 10, 1111), ("bf16", 96, 6, 1111), ("f32", 96, 6, 1111)])
 @pytest.mark.parametrize("B,T", [(1, 17), (2, 32), (5, 13), (4, 75), (4, 113), (9, 57), (40, 20)])
 def test_vocabulary_rows_are_bitwise_those_of_few_rows(dtype, d, heads, vocab, B, T):
