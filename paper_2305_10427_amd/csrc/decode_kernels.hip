@@ -334,7 +334,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH > 64 ? 2
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int n = lane & 15, g = lane >> 4;
-  const int hh = blockIdx.x, r_in = blockIdx.y * 16, s = blockIdx.z;
+  const int hh = blockIdx.x, r_in = blockIdx.y * 16, s = a.sent0 + blockIdx.z;
   // the sentence's rows: first row, rows of this tile, position of its first
   // row (loads on a straight path: unused ones read valid words of q)
   const int* any = reinterpret_cast<const int*>(a.q);
@@ -1226,16 +1226,24 @@ static hipError_t launch_attn_t(const AttnArgs& a, int grid, hipStream_t s) {
   return a.one_source ? launch_attn_f<AT, 1>(a, grid, s) : launch_attn_f<AT, 0>(a, grid, s);
 }
 
+// A launch takes at most kMaxGridZ sentences (the limit of the grid's last
+// dimension); a larger batch takes several.
+constexpr int kMaxGridZ = 65535;
+
 template <typename AT>
-static hipError_t launch_attn_tile(const AttnArgs& a, int tiles, hipStream_t s) {
-  const dim3 grid(a.H, tiles, a.n_sent);
-  switch (a.dh) {
-    case 32: hipLaunchKernelGGL((k_attn_tile<AT, 32>), grid, dim3(256), 0, s, a); break;
-    case 64: hipLaunchKernelGGL((k_attn_tile<AT, 64>), grid, dim3(256), 0, s, a); break;
-    case 128: hipLaunchKernelGGL((k_attn_tile<AT, 128>), grid, dim3(256), 0, s, a); break;
-    default: return hipErrorInvalidValue;
+static hipError_t launch_attn_tile(AttnArgs a, int tiles, hipStream_t s) {
+  hipError_t e = hipSuccess;
+  for (a.sent0 = 0; a.sent0 < a.n_sent && e == hipSuccess; a.sent0 += kMaxGridZ) {
+    const dim3 grid(a.H, tiles, std::min(a.n_sent - a.sent0, kMaxGridZ));
+    switch (a.dh) {
+      case 32: hipLaunchKernelGGL((k_attn_tile<AT, 32>), grid, dim3(256), 0, s, a); break;
+      case 64: hipLaunchKernelGGL((k_attn_tile<AT, 64>), grid, dim3(256), 0, s, a); break;
+      case 128: hipLaunchKernelGGL((k_attn_tile<AT, 128>), grid, dim3(256), 0, s, a); break;
+      default: return hipErrorInvalidValue;
+    }
+    e = hipGetLastError();
   }
-  return hipGetLastError();
+  return e;
 }
 
 // Measured (large model, 16 heads, blocks of 16; us per launch, one wave or two

@@ -144,6 +144,7 @@ struct AttnArgs {
   int sent_rows;
   const struct SentState* st;
   int n_sent;
+  int sent0;               // first sentence of this launch (set by launch_attn)
 };
 
 struct EmbedArgs {

@@ -85,6 +85,26 @@ def test_blocks_across_row_tiles_equal_single_decodes(dtype, heads, mode, block)
         np.testing.assert_array_equal(ids[b, :ln[b]], i1[0, :l1[0]])
 
 
+def test_more_sentences_than_a_grid_dimension_holds():
+    """70,000 sentences of eight rows (the attention's launches take 65,535): logits and a decode of the first, the
+    last and the sentences where the launches meet equal each sentence's own."""
+    import torch
+    cfg = dataclasses.replace(cfg_of("f32", 64, 2, 64, vocab=40), n_dec=1)
+    gm = pdec.Model(cfg, synth.make_weights(cfg, seed=8, bias_std=0.1, ln_std=0.1))
+    B, n = 70000, 8
+    g = np.random.default_rng(1)
+    src = g.integers(4, cfg.vocab, (B, n)).astype(np.int32)
+    tgt = g.integers(4, cfg.vocab, (B, n)).astype(np.int32)
+    lens = [1 + i % n for i in range(B)]
+    ctx, one = pdec.Context(gm, B, n, n), pdec.Context(gm, 1, n, n)
+    got = logits(ctx, src, lens, tgt)
+    out = [t.cpu().numpy() for t in ctx.decode("gs_jacobi", [n] * B, block=n)]
+    for b in (0, 65534, 65535, 65536, B - 1):
+        np.testing.assert_array_equal(got[b], logits(one, src[b:b + 1, :lens[b]], lens[b:b + 1], tgt[b:b + 1])[0])
+        for x, y in zip(out, one.decode("gs_jacobi", [n], block=n)):
+            np.testing.assert_array_equal(x[b], y.cpu().numpy()[0])
+
+
 def launch_bound(rows, full):
     """Rows an iteration of `rows` rows is launched (and its graph captured) for."""
     b = 1
