@@ -32,7 +32,9 @@
 //
 // Rows at or above the device row count are not stored; a workgroup whose rows
 // all lie there returns at once.
+#include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "common.h"
 #include "epilogue.h"
@@ -282,9 +284,17 @@ hipError_t launch_product(const GemmArgs& a, int cfg, hipStream_t s, bool init) 
   }
 }
 
-// The vocabulary: 32 rows x 256 columns, four waves side by side.
-template <typename WT, int EPI> hipError_t launch_vocab(const GemmArgs& a, hipStream_t s, bool init) {
-  return launch_shape<WT, EPI, 2, 4, 1, 1, 4, 4>(a, s, init);
+// The vocabulary: 16 x 64, 32 x 128 or 32 x 256 tiles, four waves side by side.
+template <typename WT, int EPI> hipError_t launch_vocab(const GemmArgs& a, int bn, hipStream_t s) {
+  if (bn == 64) return launch_shape<WT, EPI, 1, 1, 1, 1, 4, 8>(a, s, false);
+  if (bn == 128) return launch_shape<WT, EPI, 2, 2, 1, 1, 4, 4>(a, s, false);
+  if constexpr (std::is_same<WT, bf16_t>::value)
+    if (bn == 256) return launch_shape<WT, EPI, 2, 4, 1, 1, 4, 4>(a, s, false);
+  return hipErrorInvalidValue;
+}
+
+template <typename WT> hipError_t launch_vocab_w(int epi, const GemmArgs& a, int bn, hipStream_t s) {
+  return epi == EPI_ARGMAX ? launch_vocab<WT, EPI_ARGMAX>(a, bn, s) : launch_vocab<WT, EPI_LOGITS>(a, bn, s);
 }
 
 template <typename WT>
@@ -294,8 +304,6 @@ hipError_t launch_w(int epi, int ksplit, int cfg, const GemmArgs& a, hipStream_t
     case EPI_ACT: return ksplit == 8 ? launch_product<WT, EPI_ACT, 8>(a, cfg, s, init) : launch_product<WT, EPI_ACT, 4>(a, cfg, s, init);
     case EPI_RESID: return ksplit == 8 ? launch_product<WT, EPI_RESID, 8>(a, cfg, s, init) : launch_product<WT, EPI_RESID, 4>(a, cfg, s, init);
     case EPI_QKV: return ksplit == 8 ? launch_product<WT, EPI_QKV, 8>(a, cfg, s, init) : launch_product<WT, EPI_QKV, 4>(a, cfg, s, init);
-    case EPI_ARGMAX: return launch_vocab<WT, EPI_ARGMAX>(a, s, init);
-    case EPI_LOGITS: return launch_vocab<WT, EPI_LOGITS>(a, s, init);
     default: return hipErrorInvalidValue;
   }
 }
@@ -331,14 +339,24 @@ static int gemm_feed_cfg(int dtype, int N, int rows) {
   return P_32x32;
 }
 
+// Byte offsets within a tile's rows and columns (at most 256) fit 31 bits.
+static bool offsets_fit(int dtype, const GemmArgs& a) {
+  return 256ull * std::max(a.ldx, a.K) * (dtype == DT_BF16 ? 2 : 4) < (1ull << 31);
+}
+
+hipError_t launch_vocab_feed(int dtype, int epi, int bn, const GemmArgs& a, hipStream_t s) {
+  if (a.n_rows <= 0) return hipSuccess;
+  const int ks = dtype == DT_BF16 ? Mma<bf16_t>::KS : Mma<float>::KS;
+  if (epi != EPI_ARGMAX && epi != EPI_LOGITS) return hipErrorInvalidValue;
+  if (a.K % ks != 0 || a.x_f32 || a.wp == nullptr || !offsets_fit(dtype, a)) return hipErrorInvalidValue;
+  return dtype == DT_BF16 ? launch_vocab_w<bf16_t>(epi, a, bn, s) : launch_vocab_w<float>(epi, a, bn, s);
+}
+
 hipError_t launch_gemm_feed(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s) {
   if (a.n_rows <= 0) return hipSuccess;
-  const int es = dtype == DT_BF16 ? 2 : 4, ks = dtype == DT_BF16 ? Mma<bf16_t>::KS : Mma<float>::KS;
-  const bool vocab = epi == EPI_ARGMAX || epi == EPI_LOGITS;
-  if (a.K % ks != 0 || a.x_f32 || ksplit != (vocab ? 1 : (a.K >= 2048 ? 8 : 4))) return hipErrorInvalidValue;
-  if (!vocab && a.N % 16 != 0) return hipErrorInvalidValue;
-  // byte offsets within a tile's rows and columns (at most 256) fit 31 bits
-  if (256ull * std::max(a.ldx, a.K) * es >= (1ull << 31)) return hipErrorInvalidValue;
+  const int ks = dtype == DT_BF16 ? Mma<bf16_t>::KS : Mma<float>::KS;
+  if (a.K % ks != 0 || a.N % 16 != 0 || a.x_f32 || ksplit != (a.K >= 2048 ? 8 : 4)) return hipErrorInvalidValue;
+  if (!offsets_fit(dtype, a)) return hipErrorInvalidValue;
   if (a.out_feed && (epi != EPI_ACT || a.N % 32 != 0)) return hipErrorInvalidValue;
   if (!(epi == EPI_QKV && a.n_layers > 1) && a.wp == nullptr) return hipErrorInvalidValue;
   const int cfg = gemm_feed_cfg(dtype, a.N, a.n_rows);

@@ -464,26 +464,62 @@ bool stage_product(int dtype, const GemmArgs& a) {
   return tiles >= (a.K >= 2048 ? 192 : 360);
 }
 
-// The tile for a vocabulary projection of `rows` rows, S_NONE where k_gemm_feed
-// is the faster one (or as fast).  Measured, us: bf16 250,027 x 1024, argmax:
-// 32 rows feed 91, 64x256 92; 64 rows 64x256 92, 128x128 94 (feed 105); 128 rows
-// 128x128 95, 64x256 106; 256 rows 154 / 128x256 157; 400 rows 128x256 270,
-// 128x128 288; 1024 rows 508 / 562.  58,101 x 512: 128 rows feed 23, 128x128 22;
-// 160 rows 28 / 30; 200 rows 34 / 30; 1000 rows 121 / 76 (128x256 81).  Stored
-// logits: 300 rows of 1024 128x256 249, 256x256 336; 500 rows 364 / 326 (fuller
-// rows of 256 columns go out together), 4160 rows 3319 / 2796; 400 rows of 512
-// 128x128 44, 256x256 45, feed 53; 1000 rows 130 / 100 / 200.  float32 of 512 (matrix bound: 157
-// TFLOP/s): 300 rows feed 171, 128x256 210; 1120 rows 597 / 527, logits 622 / 574.
-int stage_cfg(int dtype, int epi, int K, int rows) {
-  if (dtype == DT_F32) return rows > 512 ? S_128x256 : S_NONE;
-  if (K <= 512) {
-    if (rows <= (epi == EPI_LOGITS ? 64 : 160)) return S_NONE;
-    return epi == EPI_LOGITS && rows > 512 ? S_256x256 : S_128x128;
+// The tile for a vocabulary projection of `rows` rows: the largest that leaves
+// enough workgroups.  us measured with the weights out of the caches (argmax
+// unless said; f: k_gemm_feed, s: staged, workgroups in brackets):
+//
+// f16x64 while there are few of them.  A larger tile is one long serial chain
+// of products and epilogue on few CUs: float32 V = 1000, K = 64 / 512, any rows
+// up to 256: 4.3 / 6 against f32x256 [4 to 32] 10 / 23; bf16 V = 7001, K = 640,
+// 64 rows 7.1 [440], s64x256 [28] 17.5.  It gives way to f32x128 where its
+// repeated operand reads cost more: bf16 K = 512 at 1500 (V = 8000, 192 rows
+// 10.0 / 10.2; V = 20,000, 64 rows [1252] 9.3 / 10.9, 96 rows [1878] 11.9 / 10.6),
+// K = 1024 at 750 (V = 8000, 96 rows 10.3 / 10.0; V = 32,000, 32 rows [1000] 15.2 /
+// 14.9), float32 at 1850 (V = 4003, 384 rows [1512] 12.2 / 14.6, 512 [2016] 15.7 /
+// 14.7; V = 58,101, 32 rows [1816] 24.3 / 26.1, 64 rows [3632] 41.1 / 39.1).
+// f32x256 for the bf16 vocabularies that f32x128 would cut into more than 2560
+// (K <= 512) or 6000 units of 16 x 64: V = 58,101, K = 512, 64 stored rows 14.3 / 15.6;
+// K = 1024: V = 80,000, 64 rows [5000] 33.2 / 29.9, V = 250,027, 32 stored 101.7 / 104.0.
+//
+// Staged, bf16: s128x128 from 300 workgroups (K <= 512) or 240 on: K = 512, V = 8000:
+// 512 rows [252] 17.3, f32x128 14.3, V = 20,000: 256 rows [314] 16.1 / 16.5, 384 rows
+// [471] 16.6 / 22.3; K = 1024: V = 8000, 384 rows [189] 20.2 / 17.4, V = 32,000, 128 rows
+// [250] 16.7 / 22.6.  Of few rows only: V = 58,101, K = 512, 160 rows f 28, s 30.
+// s64x256 for 33 to 64 rows where it gives more than the 512 workgroups of one
+// round: V = 250,027 90.1, s128x128 91.9; V = 80,000 [313] 37.0, f32x128 29.9.
+// s128x256, K = 1024: from 1600 on (V = 250,027, 512 rows 252, s128x128 265; V = 80,000,
+// 512 rows [1252] 87.7 / 77.7, 2048 rows [5008] 283 / 306), and where it takes one round
+// and s128x128 (768 a round) two (V = 32,000, 512 rows [500] 31.8 / 35.1); stored logits
+// from 900 on (V = 250,027, 256 rows 181 / 197; V = 80,000, 384 rows [939] 87 / 93, 256 rows
+// [626] 56 / 47).  s256x256 for stored logits (fuller rows of 256 columns go out
+// together) from 240 on: V = 58,101, K = 512, 512 rows [454] 48, s128x128 61; V = 32,000,
+// 512 rows [250] 35 / 46; V = 8000, 1024 rows [128] 29 / 21.
+// float32, bound by the matrix units: s128x256 for 1536 rows and 480 workgroups on:
+// V = 8000, 2048 rows [512] 131, f32x128 137; V = 58,101, 1024 rows 499 / 470, 2048 919 / 944.
+struct VocabTile {
+  int cfg;   // staged, or S_NONE: k_gemm_feed
+  int bn;    // columns of a workgroup
+};
+
+VocabTile vocab_tile(int dtype, int epi, int V, int K, int rows) {
+  const auto wgs = [&](int bm, int bn) {
+    return static_cast<long long>((rows + bm - 1) / bm) * ((V + bn - 1) / bn);
+  };
+  const bool store = epi == EPI_LOGITS, wide = K > 512;
+  if (dtype == DT_F32) {
+    if (rows >= 1536 && wgs(128, 256) >= 480) return {S_128x256, 256};
+    return {S_NONE, wgs(16, 64) <= 1850 ? 64 : 128};
   }
-  if (rows <= 32) return S_NONE;
-  if (rows <= 64) return S_64x256;
-  if (epi == EPI_LOGITS) return rows > 448 ? S_256x256 : S_128x256;
-  return rows <= 256 ? S_128x128 : S_128x256;
+  if (store && rows > 448 && wgs(256, 256) >= 240) return {S_256x256, 256};
+  if (wide) {
+    const long long big = wgs(128, 256);
+    if (store ? rows > 128 && big >= 900 : rows > 256 && (big >= 1600 || (big <= 512 && wgs(128, 128) > 768)))
+      return {S_128x256, 256};
+    if (rows > 32 && rows <= 64 && wgs(64, 256) > 512) return {S_64x256, 256};
+  }
+  if (rows > (wide || store ? 64 : 160) && wgs(128, 128) >= (wide ? 240 : 300)) return {S_128x128, 128};
+  const long long u = wgs(16, 64);
+  return {S_NONE, u <= (wide ? 750 : 1500) ? 64 : u <= (wide ? 6000 : 2560) ? 128 : 256};
 }
 
 }  // namespace
@@ -502,7 +538,7 @@ hipError_t gemm_stage_init() {
 }
 
 int vocab_rows_parts(int dtype, int V, int K, int rows) {
-  const int bn = stage_cfg(dtype, EPI_ARGMAX, K, rows) == S_128x128 ? 128 : 256;   // k_gemm_feed: 256
+  const int bn = vocab_tile(dtype, EPI_ARGMAX, V, K, rows).bn;
   return (V + bn - 1) / bn;
 }
 
@@ -510,12 +546,12 @@ hipError_t launch_vocab_rows(int dtype, int epi, const GemmArgs& a, hipStream_t 
   if (a.n_rows <= 0) return hipSuccess;
   if (epi != EPI_ARGMAX && epi != EPI_LOGITS) return hipErrorInvalidValue;
   if (epi == EPI_ARGMAX && a.part_ld < vocab_rows_parts(dtype, a.N, a.K, a.n_rows)) return hipErrorInvalidValue;
-  const int cfg = stage_cfg(dtype, epi, a.K, a.n_rows);
-  if (cfg == S_NONE) return launch_gemm_feed(dtype, epi, 1, a, s);
+  const VocabTile t = vocab_tile(dtype, epi, a.N, a.K, a.n_rows);
+  if (t.cfg == S_NONE) return launch_vocab_feed(dtype, epi, t.bn, a, s);
   const int es = dtype == DT_BF16 ? 2 : 4, ks = dtype == DT_BF16 ? Mma<bf16_t>::KS : Mma<float>::KS;
   if (a.K % ks != 0 || a.x_f32 || !a.x_feed || a.wp == nullptr) return hipErrorInvalidValue;
   if (256ull * a.K * es >= (1ull << 31)) return hipErrorInvalidValue;   // byte offsets within a tile fit 31 bits
-  return dtype == DT_BF16 ? launch_w<bf16_t>(epi, cfg, a, s, false) : launch_w<float>(epi, cfg, a, s, false);
+  return dtype == DT_BF16 ? launch_w<bf16_t>(epi, t.cfg, a, s, false) : launch_w<float>(epi, t.cfg, a, s, false);
 }
 
 hipError_t launch_product_rows(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s) {

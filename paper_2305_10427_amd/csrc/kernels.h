@@ -302,9 +302,11 @@ size_t gemm_ln_lds_bytes(int K, size_t elt);
 // Products of many rows and the vocabulary projection of more than 16 rows
 // without LDS staging: weights from their feed-order copy (wp; lw of a
 // multi-layer launch), inputs in feed order (x_feed) or row-major; bitwise the
-// same values as launch_gemm.  The argmax writes ceil(N / 256) partials per row.
+// same values as launch_gemm.  The vocabulary's tiles have bn columns (64, 128;
+// bf16 also 256); its argmax writes ceil(N / bn) partials per row.
 hipError_t gemm_feed_init();   // once before the first launch
 hipError_t launch_gemm_feed(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s);
+hipError_t launch_vocab_feed(int dtype, int epi, int bn, const GemmArgs& a, hipStream_t s);
 // The layers' products of many rows: launch_gemm_feed, or staged tiles where they are faster.
 hipError_t launch_product_rows(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s);
 // The vocabulary projection (EPI_ARGMAX, EPI_LOGITS) of more than 16 rows in

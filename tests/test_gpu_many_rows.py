@@ -162,16 +162,44 @@ def test_vocabulary_rows_are_bitwise_those_of_few_rows(dtype, d, heads, vocab, B
     compare(cfg_of(dtype, d, heads, 128, vocab=vocab), B, 7, T)
 
 
+@pytest.mark.parametrize("dtype,d,heads,vocab,B,T", [
+    ("f32", 64, 4, 1000, 1, 33), ("f32", 64, 4, 1000, 7, 33),            # LayerNorm in the product; 16 x 64 tiles
+    ("f32", 96, 6, 20011, 4, 28), ("f32", 96, 6, 20011, 24, 65),         # 32 x 128; staged 128 x 256
+    ("bf16", 96, 6, 20011, 2, 40), ("bf16", 96, 6, 58001, 2, 32),        # 32 x 128; 32 x 256
+    ("bf16", 96, 6, 20011, 10, 30), ("bf16", 96, 6, 20011, 10, 80),      # staged 128 x 128; 256 x 256
+    ("bf16", 640, 10, 20011, 3, 16), ("bf16", 640, 10, 20011, 5, 26),    # 32 x 128; staged 128 x 128
+    ("bf16", 640, 10, 58001, 7, 64), ("bf16", 544, 17, 131200, 3, 21)])  # staged 128 x 256; 64 x 256
+def test_each_vocabulary_tile_gives_the_rows_of_few_rows(dtype, d, heads, vocab, B, T):
+    """Stored logits on every tile that the vocabulary's size, the width and the rows select, ragged columns and rows."""
+    compare(dataclasses.replace(cfg_of(dtype, d, heads, 64, vocab=vocab), n_dec=1), B, 5, T)
+
+
+@pytest.mark.parametrize("dtype,d,heads,vocab,B,m", [
+    ("f32", 128, 2, 20011, 9, 28), ("f32", 128, 2, 20011, 26, 60),       # 32 x 128; staged 128 x 256
+    ("bf16", 128, 2, 20011, 5, 13), ("bf16", 128, 2, 20011, 9, 16),      # 32 x 128; 32 x 256
+    ("bf16", 128, 2, 20011, 9, 28), ("bf16", 640, 10, 20011, 9, 60),     # staged 128 x 128; 128 x 256
+    ("bf16", 544, 17, 131200, 3, 13)])                                   # staged 64 x 256
+def test_argmax_of_planted_logits_on_each_vocabulary_tile(dtype, d, heads, vocab, B, m):
+    cfg = dataclasses.replace(cfg_of(dtype, d, heads, 64, vocab=vocab), n_dec=1, logit_scale=0.0)
+    v = vocab
+    planted(cfg, B, m, [(2.5, (v - 300, v - 299, v - 1), None), (0.0, (300, 5555, v - 81), None), (1.0, (v - 1,), None),
+                        (0.5, (513,), v - 20)])
+
+
 @pytest.mark.parametrize("dtype,d,heads", [("bf16", 640, 10), ("bf16", 128, 2), ("f32", 128, 2)])
 @pytest.mark.parametrize("B,m", [(1, 17), (3, 16), (5, 13), (9, 28), (9, 60)])
 def test_argmax_of_planted_logits(dtype, d, heads, B, m):
     """Logits that are the output bias alone (scale 0): the largest, the lowest index among equals (at zero too,
     where the order of +0 and -0 must not matter), and the flag of a non-finite one."""
-    import torch
     cfg = dataclasses.replace(cfg_of(dtype, d, heads, 128, vocab=1111), logit_scale=0.0)
-    for best, at, bad in [(2.5, (700, 701, 1110), None), (0.0, (300, 555, 1030), None), (1.0, (1110,), None),
-                          (0.5, (513,), 20)]:
-        w = synth.make_weights(cfg, seed=3)
+    planted(cfg, B, m, [(2.5, (700, 701, 1110), None), (0.0, (300, 555, 1030), None), (1.0, (1110,), None),
+                        (0.5, (513,), 20)])
+
+
+def planted(cfg, B, m, cases):
+    import torch
+    w = synth.make_weights(cfg, seed=3)
+    for best, at, bad in cases:
         bias = np.full(cfg.vocab, -1.0, np.float32)
         bias[list(at)] = best
         if bad is not None:
