@@ -292,6 +292,17 @@ bool many_rows(const pd_model& M, int R_max) { return R_max > stream_max_rows(M.
 // x 1024 295 -> 102 us, 58,101 x 512 36 -> 13 us against the general kernel).
 constexpr int kVocabStreamMaxRows = 16;
 
+// Whether the stored logits of a launch run on launch_vocab_rows.  The smallest
+// ones (16 x 64 tiles times d up to 16,384) stay on the general kernel with the
+// LayerNorm in its prologue: a scoring call of such a model is bound by the
+// host's launches, and one launch less is worth more than the tile (V = 1000,
+// d = 64, 64 rows: 103.0 us a call, 107.5 with the launch; V = 1111, d = 128, 32 rows
+// 126.4 / 130.5, 96 rows the same; V = 4003, d = 256, 32 rows 135.6 / 134.5).
+bool logits_on_rows(const pd_model& M, int R_max) {
+  const long long tiles = static_cast<long long>((R_max + 15) / 16) * ((M.V + 63) / 64);
+  return R_max > kVocabStreamMaxRows && (many_rows(M, R_max) || tiles * M.d > 16384);
+}
+
 // One matrix product of the layers.  pro_ln: normalise x (float if x_f32) with
 // (lg, lb) first; for many rows the LayerNorm runs as its own kernel into
 // feed_tmp (feed order; g.ln_out also gets the rows).
@@ -299,7 +310,7 @@ hipError_t run_gemm(pd_ctx& C, const Rows& r, GemmArgs g, int epi, bool pro_ln, 
                     hipStream_t s) {
   const pd_model& M = *C.M;
   int pro = PRO_NONE;
-  const bool vocab = epi == EPI_LOGITS && r.R_max > kVocabStreamMaxRows;
+  const bool vocab = epi == EPI_LOGITS && logits_on_rows(M, r.R_max);
   const bool many = vocab || many_rows(M, r.R_max);
   if (pro_ln) {
     if (!many) {
