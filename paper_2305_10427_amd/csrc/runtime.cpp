@@ -34,13 +34,23 @@ pd_status fail(pd_status st, const std::string& msg) {
       return fail(PD_E_DEVICE, std::string(#call " failed: ") + hipGetErrorString(e_));     \
   } while (0)
 
-// Up to this many rows a product runs on the streaming kernel with the
+// Up to this many rows a product runs on the row-streaming kernel with the
 // LayerNorm in its prologue; above it the LayerNorm runs as its own kernel and
-// bf16 products on the LDS-tiled kernel.  Both choices give bitwise the same
-// rows.  For d <= 512 the streaming kernel stays ahead up to 128 rows; for
-// wider models its per-workgroup LayerNorm costs more than the separate pass
-// from 65 rows on.
-int stream_max_rows(int d) { return d <= 512 ? 128 : 64; }
+// the products on the many-row kernels.  Both choices give bitwise the same
+// rows.  For d > 512 the repeated LayerNorm costs more than the separate pass
+// from 65 rows on.  Up to 512 the streaming kernel is ahead, or level, to 128
+// rows, and with float32 up to d = 256, where the many-row tiles are few, to 192
+// or 256 (us per GS-Jacobi iteration of that many rows, streaming / many-row):
+//   float32 d = 512, 6 layers   96 rows 375 / 407, 128 402 / 429, 192 505 / 477
+//   bfloat16 d = 512, 6 layers  64 rows 241 / 243, 128 247 / 244, 192 257 / 249
+//   bfloat16 d = 256, 3 layers  128 rows 124 / 125, 192 143 / 130
+//   float32 d = 256, 3 layers   64 rows 128 / 158, 128 136 / 155, 192 154 / 167, 256 156 / 161
+//   float32 d = 128, 3 layers   64 rows 118 / 140, 128 118 / 134, 192 136 / 137, 256 143 / 141
+//   float32 d = 64, 2 layers    192 rows 83 / 92, 256 85 / 93
+int stream_max_rows(int dtype, int d) {
+  if (d > 512) return 64;
+  return dtype == DT_BF16 || d > 256 ? 128 : d > 64 ? 192 : 256;
+}
 constexpr size_t kAlign = 256;
 constexpr long long kMaxCtxRows = 1LL << 24;   // rows of the largest launch a context may need
 
@@ -284,7 +294,7 @@ GemmArgs gemm_base(const Rows& r) {
 
 // Whether an iteration's products run on the many-row kernel (gemm_feed),
 // every LayerNorm as its own kernel writing the feed order it reads.
-bool many_rows(const pd_model& M, int R_max) { return R_max > stream_max_rows(M.d); }
+bool many_rows(const pd_model& M, int R_max) { return R_max > stream_max_rows(M.dt, M.d); }
 
 // Iterations of at most one 16-row tile use the streaming vocabulary kernel
 // (vocab_grid partials per row); above it the vocabulary projection runs after
