@@ -268,9 +268,9 @@ pd_status pd_ctx_vocab_timing(const pd_ctx* ctx, int64_t* launches, double* tota
 /*
  * Timing of the decoder's matrix products.  With timing enabled, every
  * decoder-layer product of a timed iteration that runs on the streaming
- * product kernel (iterations of up to 64 rows, 128 for d_model <= 512, for
- * float32 models 192 for d_model <= 256 and 256 for d_model <= 64: QKV,
- * attention output, cross-attention query and output, both FFN products) is
+ * product kernel (iterations of up to 64 rows, 128 for d_model <= 512, 256
+ * for float32 models of d_model <= 64: QKV, attention output, cross-attention
+ * query and output, both FFN products) is
  * launched with a pair of events that carry its dispatch's own start and end
  * times.  pd_ctx_product_timing returns, since the last pd_ctx_set_timing,
  * their number, the sum of their durations in milliseconds, and the

@@ -464,6 +464,16 @@ bool stage_product(int dtype, const GemmArgs& a) {
   return tiles >= (a.K >= 2048 ? 192 : 360);
 }
 
+// Whether a float32 product gives k_gemm_feed too few 32 x 32 tiles for the 256
+// CUs; k_gemm, with a workgroup per 16 x 16, is the faster one then.  us per
+// iteration of three layers, k_gemm_feed / k_gemm below 96 tiles: d = 256, 224
+// rows 173 / 159, 256 rows 164 / 152, 320 rows 172 / 162; d = 128, 256 rows 141 / 134,
+// 448 rows 152 / 146, 576 rows 146 / 146, 768 rows (96 tiles in k_gemm too) 152 / 156.
+bool few_tiles(int dtype, const GemmArgs& a) {
+  return dtype == DT_F32 && a.n_layers <= 1 &&
+         static_cast<long long>((a.n_rows + 31) / 32) * ((a.N + 31) / 32) < 96;
+}
+
 // The tile for a vocabulary projection of `rows` rows: the largest that leaves
 // enough workgroups.  us measured with the weights out of the caches (argmax
 // unless said; f: k_gemm_feed, s: staged, workgroups in brackets):
@@ -556,6 +566,7 @@ hipError_t launch_vocab_rows(int dtype, int epi, const GemmArgs& a, hipStream_t 
 
 hipError_t launch_product_rows(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s) {
   if (a.n_rows <= 0) return hipSuccess;
+  if (few_tiles(dtype, a)) return launch_gemm(dtype, PRO_NONE, epi, ksplit, a, s, nullptr, nullptr);
   if (!stage_product(dtype, a)) return launch_gemm_feed(dtype, epi, ksplit, a, s);
   if (a.K % Mma<bf16_t>::KS != 0 || a.x_f32 || ksplit != (a.K >= 2048 ? 8 : 4) || a.N % 16 != 0) return hipErrorInvalidValue;
   if (256ull * a.K * sizeof(bf16_t) >= (1ull << 31)) return hipErrorInvalidValue;

@@ -307,7 +307,8 @@ size_t gemm_ln_lds_bytes(int K, size_t elt);
 hipError_t gemm_feed_init();   // once before the first launch
 hipError_t launch_gemm_feed(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s);
 hipError_t launch_vocab_feed(int dtype, int epi, int bn, const GemmArgs& a, hipStream_t s);
-// The layers' products of many rows: launch_gemm_feed, or staged tiles where they are faster.
+// The layers' products of many rows: launch_gemm_feed, or staged tiles or
+// launch_gemm where they are faster.
 hipError_t launch_product_rows(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s);
 // The vocabulary projection (EPI_ARGMAX, EPI_LOGITS) of more than 16 rows in
 // feed order, on the kernel that suits the rows; the argmax writes

@@ -39,18 +39,15 @@ pd_status fail(pd_status st, const std::string& msg) {
 // the products on the many-row kernels.  Both choices give bitwise the same
 // rows.  For d > 512 the repeated LayerNorm costs more than the separate pass
 // from 65 rows on.  Up to 512 the streaming kernel is ahead, or level, to 128
-// rows, and with float32 up to d = 256, where the many-row tiles are few, to 192
-// or 256 (us per GS-Jacobi iteration of that many rows, streaming / many-row):
-//   float32 d = 512, 6 layers   96 rows 375 / 407, 128 402 / 429, 192 505 / 477
+// rows, and for float32 of d <= 64 to 256 (us per GS-Jacobi iteration of that
+// many rows, streaming / many-row):
+//   float32 d = 512, 2 layers   64 rows 108 / 111, 128 115 / 114, 256 151 / 142
 //   bfloat16 d = 512, 6 layers  64 rows 241 / 243, 128 247 / 244, 192 257 / 249
 //   bfloat16 d = 256, 3 layers  128 rows 124 / 125, 192 143 / 130
-//   float32 d = 256, 3 layers   64 rows 128 / 158, 128 136 / 155, 192 154 / 167, 256 156 / 161
-//   float32 d = 128, 3 layers   64 rows 118 / 140, 128 118 / 134, 192 136 / 137, 256 143 / 141
-//   float32 d = 64, 2 layers    192 rows 83 / 92, 256 85 / 93
-int stream_max_rows(int dtype, int d) {
-  if (d > 512) return 64;
-  return dtype == DT_BF16 || d > 256 ? 128 : d > 64 ? 192 : 256;
-}
+//   float32 d = 256, 3 layers   64 rows 128 / 136, 128 136 / 140, 192 154 / 152, 256 159 / 148
+//   float32 d = 128, 3 layers   64 rows 118 / 128, 128 117 / 121, 192 136 / 129, 256 144 / 134
+//   float32 d = 64, 2 layers    64 rows 86 / 92, 192 84 / 87, 256 85 / 89
+int stream_max_rows(int dtype, int d) { return d > 512 ? 64 : d <= 64 && dtype == DT_F32 ? 256 : 128; }
 constexpr size_t kAlign = 256;
 constexpr long long kMaxCtxRows = 1LL << 24;   // rows of the largest launch a context may need
 

@@ -220,6 +220,14 @@ def test_staged_products_are_bitwise_those_of_few_rows(d, heads, d_ff, B, T):
     compare(dataclasses.replace(cfg_of("bf16", d, heads, d_ff), n_dec=1), B, 64, T)
 
 
+@pytest.mark.parametrize("pre_ln", [True, False])
+@pytest.mark.parametrize("d,d_ff,B,T", [(128, 2048, 3, 43), (128, 512, 3, 43), (64, 96, 9, 29), (128, 2048, 23, 32),
+                                        (128, 512, 24, 32)])
+def test_float32_products_of_few_tiles_are_bitwise_those_of_few_rows(pre_ln, d, d_ff, B, T):
+    """More rows than the streaming products take, fewer than 96 tiles of 32 x 32 (the last two: 92 and 96 for N = 128)."""
+    compare(cfg_of("f32", d, 4, d_ff, pre_ln=pre_ln), B, 20, T)
+
+
 @pytest.mark.parametrize("dtype,d,heads,d_ff", [("bf16", 256, 4, 2048), ("f32", 128, 4, 4096), ("bf16", 128, 2, 512),
                                                 ("f32", 256, 4, 1024), ("bf16", 1024, 16, 4096)])
 @pytest.mark.parametrize("T", [1, 2, 7, 8, 9, 16])
