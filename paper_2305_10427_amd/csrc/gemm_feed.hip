@@ -339,16 +339,11 @@ static int gemm_feed_cfg(int dtype, int N, int rows) {
   return P_32x32;
 }
 
-// Byte offsets within a tile's rows and columns (at most 256) fit 31 bits.
-static bool offsets_fit(int dtype, const GemmArgs& a) {
-  return 256ull * std::max(a.ldx, a.K) * (dtype == DT_BF16 ? 2 : 4) < (1ull << 31);
-}
-
 hipError_t launch_vocab_feed(int dtype, int epi, int bn, const GemmArgs& a, hipStream_t s) {
   if (a.n_rows <= 0) return hipSuccess;
   const int ks = dtype == DT_BF16 ? Mma<bf16_t>::KS : Mma<float>::KS;
   if (epi != EPI_ARGMAX && epi != EPI_LOGITS) return hipErrorInvalidValue;
-  if (a.K % ks != 0 || a.x_f32 || a.wp == nullptr || !offsets_fit(dtype, a)) return hipErrorInvalidValue;
+  if (a.K % ks != 0 || a.x_f32 || a.wp == nullptr || !tile_offsets_fit(dtype, a)) return hipErrorInvalidValue;
   return dtype == DT_BF16 ? launch_vocab_w<bf16_t>(epi, a, bn, s) : launch_vocab_w<float>(epi, a, bn, s);
 }
 
@@ -356,7 +351,7 @@ hipError_t launch_gemm_feed(int dtype, int epi, int ksplit, const GemmArgs& a, h
   if (a.n_rows <= 0) return hipSuccess;
   const int ks = dtype == DT_BF16 ? Mma<bf16_t>::KS : Mma<float>::KS;
   if (a.K % ks != 0 || a.N % 16 != 0 || a.x_f32 || ksplit != (a.K >= 2048 ? 8 : 4)) return hipErrorInvalidValue;
-  if (!offsets_fit(dtype, a)) return hipErrorInvalidValue;
+  if (!tile_offsets_fit(dtype, a)) return hipErrorInvalidValue;
   if (a.out_feed && (epi != EPI_ACT || a.N % 32 != 0)) return hipErrorInvalidValue;
   if (!(epi == EPI_QKV && a.n_layers > 1) && a.wp == nullptr) return hipErrorInvalidValue;
   const int cfg = gemm_feed_cfg(dtype, a.N, a.n_rows);

@@ -558,18 +558,19 @@ hipError_t launch_vocab_rows(int dtype, int epi, const GemmArgs& a, hipStream_t 
   if (epi == EPI_ARGMAX && a.part_ld < vocab_rows_parts(dtype, a.N, a.K, a.n_rows)) return hipErrorInvalidValue;
   const VocabTile t = vocab_tile(dtype, epi, a.N, a.K, a.n_rows);
   if (t.cfg == S_NONE) return launch_vocab_feed(dtype, epi, t.bn, a, s);
-  const int es = dtype == DT_BF16 ? 2 : 4, ks = dtype == DT_BF16 ? Mma<bf16_t>::KS : Mma<float>::KS;
+  const int ks = dtype == DT_BF16 ? Mma<bf16_t>::KS : Mma<float>::KS;
   if (a.K % ks != 0 || a.x_f32 || !a.x_feed || a.wp == nullptr) return hipErrorInvalidValue;
-  if (256ull * a.K * es >= (1ull << 31)) return hipErrorInvalidValue;   // byte offsets within a tile fit 31 bits
+  if (!tile_offsets_fit(dtype, a)) return hipErrorInvalidValue;
   return dtype == DT_BF16 ? launch_w<bf16_t>(epi, t.cfg, a, s, false) : launch_w<float>(epi, t.cfg, a, s, false);
 }
 
 hipError_t launch_product_rows(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s) {
   if (a.n_rows <= 0) return hipSuccess;
-  if (few_tiles(dtype, a)) return launch_gemm(dtype, PRO_NONE, epi, ksplit, a, s, nullptr, nullptr);
+  if (few_tiles(dtype, a) || (a.n_layers <= 1 && !tile_offsets_fit(dtype, a)))
+    return launch_gemm(dtype, PRO_NONE, epi, ksplit, a, s, nullptr, nullptr);
   if (!stage_product(dtype, a)) return launch_gemm_feed(dtype, epi, ksplit, a, s);
   if (a.K % Mma<bf16_t>::KS != 0 || a.x_f32 || ksplit != (a.K >= 2048 ? 8 : 4) || a.N % 16 != 0) return hipErrorInvalidValue;
-  if (256ull * a.K * sizeof(bf16_t) >= (1ull << 31)) return hipErrorInvalidValue;
+  if (!tile_offsets_fit(dtype, a)) return hipErrorInvalidValue;
   if (a.out_feed && (epi != EPI_ACT || a.N % 32 != 0)) return hipErrorInvalidValue;
   if (!(epi == EPI_QKV && a.n_layers > 1) && a.wp == nullptr) return hipErrorInvalidValue;
   switch (epi) {

@@ -307,8 +307,14 @@ size_t gemm_ln_lds_bytes(int K, size_t elt);
 hipError_t gemm_feed_init();   // once before the first launch
 hipError_t launch_gemm_feed(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s);
 hipError_t launch_vocab_feed(int dtype, int epi, int bn, const GemmArgs& a, hipStream_t s);
+// Whether byte offsets within a many-row tile's rows and columns (at most 256)
+// fit 31 bits: K up to 4,194,303 (bf16), 2,097,151 (float32).
+inline bool tile_offsets_fit(int dtype, const GemmArgs& a) {
+  const unsigned long long ld = a.ldx > a.K ? a.ldx : a.K;
+  return 256 * ld * (dtype == DT_BF16 ? 2 : 4) < (1ull << 31);
+}
 // The layers' products of many rows: launch_gemm_feed, or staged tiles or
-// launch_gemm where they are faster.
+// launch_gemm where they are faster; launch_gemm where the offsets don't fit.
 hipError_t launch_product_rows(int dtype, int epi, int ksplit, const GemmArgs& a, hipStream_t s);
 // The vocabulary projection (EPI_ARGMAX, EPI_LOGITS) of more than 16 rows in
 // feed order, on the kernel that suits the rows; the argmax writes

@@ -220,6 +220,23 @@ def test_staged_products_are_bitwise_those_of_few_rows(d, heads, d_ff, B, T):
     compare(dataclasses.replace(cfg_of("bf16", d, heads, d_ff), n_dec=1), B, 64, T)
 
 
+def test_an_ffn_wider_than_a_tiles_offsets():
+    """d_ff of 2^22, whose rows a many-row tile cannot address: the product goes to the kernel that can."""
+    cfg = dataclasses.replace(cfg_of("bf16", 32, 1, 64), n_dec=1)
+    small, wide = synth.make_weights(cfg, seed=2, bias_std=0.1), dataclasses.replace(cfg, d_ff=1 << 22)
+    bits = {n: np.resize(small.bf16_bits[n], s) for n, s in C.param_shapes(wide)}
+    shapes = {n: np.broadcast_to(np.float32(0), s) for n, s in C.param_shapes(wide)}
+    gm = pdec.Model(wide, synth.Weights(wide, shapes, bits))
+    g = np.random.default_rng(5)
+    B, T = 9, 16
+    src, tgt = (g.integers(4, cfg.vocab, (B, x)).astype(np.int32) for x in (3, T))
+    got = logits(pdec.Context(gm, B, 3, T), src, [3] * B, tgt)
+    one = pdec.Context(gm, 1, 3, T)
+    assert np.isfinite(got).all()
+    for b in (0, B - 1):
+        np.testing.assert_array_equal(got[b], logits(one, src[b:b + 1], [3], tgt[b:b + 1])[0])
+
+
 @pytest.mark.parametrize("pre_ln", [True, False])
 @pytest.mark.parametrize("d,d_ff,B,T", [(128, 2048, 3, 43), (128, 512, 3, 43), (64, 96, 9, 29), (128, 2048, 23, 32),
                                         (128, 512, 24, 32)])
