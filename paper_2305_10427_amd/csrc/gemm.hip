@@ -464,6 +464,7 @@ hipError_t launch_gemm(int dtype, int pro, int epi, int ksplit, const GemmArgs& 
                        hipEvent_t ev1) {
   if (a.n_rows <= 0) return hipSuccess;
   if ((epi == EPI_LOGITS) != (ksplit == 1)) return hipErrorInvalidValue;
+  if (a.n_layers > 1 && a.lw_feed) return hipErrorInvalidValue;
   if (a.x_feed && (pro == PRO_LN || a.x_f32 || ksplit == 1)) return hipErrorInvalidValue;
   if (a.out_feed && (epi != EPI_ACT || ksplit == 1 || a.N % 32 != 0)) return hipErrorInvalidValue;
   const int ks = dtype == DT_BF16 ? Mma<bf16_t>::KS : Mma<float>::KS;

@@ -353,7 +353,7 @@ hipError_t launch_gemm_feed(int dtype, int epi, int ksplit, const GemmArgs& a, h
   if (a.K % ks != 0 || a.N % 16 != 0 || a.x_f32 || ksplit != (a.K >= 2048 ? 8 : 4)) return hipErrorInvalidValue;
   if (!tile_offsets_fit(dtype, a)) return hipErrorInvalidValue;
   if (a.out_feed && (epi != EPI_ACT || a.N % 32 != 0)) return hipErrorInvalidValue;
-  if (!(epi == EPI_QKV && a.n_layers > 1) && a.wp == nullptr) return hipErrorInvalidValue;
+  if (epi == EPI_QKV && a.n_layers > 1 ? !a.lw_feed : a.wp == nullptr) return hipErrorInvalidValue;
   const int cfg = gemm_feed_cfg(dtype, a.N, a.n_rows);
   return dtype == DT_BF16 ? launch_w<bf16_t>(epi, ksplit, cfg, a, s, false)
                           : launch_w<float>(epi, ksplit, cfg, a, s, false);

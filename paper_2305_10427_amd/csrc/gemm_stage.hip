@@ -572,7 +572,7 @@ hipError_t launch_product_rows(int dtype, int epi, int ksplit, const GemmArgs& a
   if (a.K % Mma<bf16_t>::KS != 0 || a.x_f32 || ksplit != (a.K >= 2048 ? 8 : 4) || a.N % 16 != 0) return hipErrorInvalidValue;
   if (!tile_offsets_fit(dtype, a)) return hipErrorInvalidValue;
   if (a.out_feed && (epi != EPI_ACT || a.N % 32 != 0)) return hipErrorInvalidValue;
-  if (!(epi == EPI_QKV && a.n_layers > 1) && a.wp == nullptr) return hipErrorInvalidValue;
+  if (epi == EPI_QKV && a.n_layers > 1 ? !a.lw_feed : a.wp == nullptr) return hipErrorInvalidValue;
   switch (epi) {
     case EPI_F32: return launch_product<EPI_F32>(a, ksplit, s);
     case EPI_ACT: return launch_product<EPI_ACT>(a, ksplit, s);

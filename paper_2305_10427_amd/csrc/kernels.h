@@ -87,14 +87,16 @@ struct GemmArgs {
   float2* part_lse;
   // EPI_QKV of several layers in one launch (n_layers > 1; the last grid
   // dimension indexes the layer): layer z reads lw[z], lb[z] and writes the
-  // caches kc / vc + z * kv_stride bytes
+  // caches kc / vc + z * kv_stride bytes.  lw_feed: lw in feed order (the
+  // many-row kernels) instead of row-major (launch_gemm); each refuses the other
   int n_layers;
+  int lw_feed;
   long long kv_stride;
   const void* lw[kMaxLayers];
   const void* lb[kMaxLayers];
-  // optional (nullptr: row-major w only): the same weights in the MFMA feed
-  // order of the K-split product kernels (launch_pack_feed); single-layer
-  // launches with N % 16 == 0 only, and the vocabulary kernel (any N)
+  // the same weights in the MFMA feed order (launch_pack_feed) of a single-layer
+  // launch: launch_gemm (N % 16 == 0) and the streaming vocabulary kernel read
+  // them in place of w if given, the many-row kernels need them
   const void* wp;
 };
 

@@ -612,9 +612,10 @@ hipError_t encoder_pass(pd_ctx& C, const int32_t* src, int B, int n_max, const i
     g.kc = C.at<char>(C.L.cross_k) + l0 * cross_layer; g.vc = C.at<char>(C.L.cross_v) + l0 * cross_layer;
     g.H = M.H; g.dh = M.dh; g.T = C.max_src; g.d = d;
     g.n_layers = nl;
+    g.lw_feed = many_rows(M, R) ? 1 : 0;
     g.kv_stride = static_cast<long long>(cross_layer);
     for (int z = 0; z < nl; ++z) {
-      g.lw[z] = many_rows(M, R) ? M.dec_feed(l0 + z, D_CWKV) : M.dec(l0 + z, D_CWKV);
+      g.lw[z] = g.lw_feed ? M.dec_feed(l0 + z, D_CWKV) : M.dec(l0 + z, D_CWKV);
       g.lb[z] = M.dec(l0 + z, D_CBKV);
     }
     if ((e = run_gemm(C, r, g, EPI_QKV, true, a_buf, s)) != hipSuccess) return e;
