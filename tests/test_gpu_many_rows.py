@@ -1,7 +1,8 @@
 """The kernels of launches with many rows give bitwise the rows of the few-row
 kernels (whose values the oracle tests judge): teacher-forced logits of a
-ragged batch against each sentence alone in at most 16 rows, at the edges of
-row tiles, key chunks and column tiles."""
+ragged batch against each sentence alone (its first positions in at most 16
+rows, and all of them), at the edges of row tiles, key chunks and column tiles;
+decodes that reuse a context's captured iterations."""
 import dataclasses
 
 import numpy as np
@@ -24,7 +25,9 @@ def logits(ctx, src, lens, tgt):
 
 
 def compare(cfg, B, n, T, seed=1, plant=None):
-    """Logits of B sentences of T positions against the same prefix evaluated 16 rows at a time at most."""
+    """Logits of B sentences of T positions against each sentence alone: its first positions in at most 16 rows, and
+    all of them in T rows (attention row by row: T * heads < 2048), so every row tile and key chunk is compared."""
+    assert T * cfg.n_heads < 2048
     w = synth.make_weights(cfg, seed=seed, bias_std=0.3, ln_std=0.2)
     if plant is not None:                       # a token whose embedding is not finite
         w.values["emb"][plant] = np.nan
@@ -44,6 +47,8 @@ def compare(cfg, B, n, T, seed=1, plant=None):
     for b in range(0, B, max(1, B // 7)):
         want = logits(one, src[b:b + 1, :lens[b]], lens[b:b + 1], tgt[b:b + 1, :t])
         np.testing.assert_array_equal(got[b, :t], want[0])
+        if T > t:
+            np.testing.assert_array_equal(got[b], logits(one, src[b:b + 1, :lens[b]], lens[b:b + 1], tgt[b:b + 1])[0])
     if plant is not None:
         assert np.isfinite(got[:, :T // 2, :plant]).all() and not np.isfinite(got[:, T // 2]).any()
     return got
