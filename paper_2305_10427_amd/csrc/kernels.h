@@ -141,7 +141,7 @@ struct AttnArgs {
   int max_keys;            // host bound on any row's key count (0: unknown); chooses the launch shape only
   int one_source;          // 1: every row is of sentence 0 and non-causal (a batch of one): key slots are
                            // loaded before klen[0] arrives (the caches must hold finite values throughout)
-  // 16-row tiles (attn_tiled): a host bound on the rows of one sentence (0: unknown), and for rows placed by a
+  // 16-row tiles (attn_row_tiles): a host bound on the rows of one sentence (0: unknown), and for rows placed by a
   // list the control step's sentence states (row0, L, i of the current rows) and their number
   int sent_rows;
   const struct SentState* st;

@@ -547,7 +547,7 @@ hipError_t encoder_pass(pd_ctx& C, const int32_t* src, int B, int n_max, const i
   }
   if ((e = launch_embed(M.dt, ea, R, s)) != hipSuccess) return e;
   // Every LayerNorm feeding a product runs in that product's prologue (a
-  // separate kernel above 64 rows, run_gemm); post-LN stores the normalised
+  // separate kernel above the streaming row bound, run_gemm); post-LN stores the normalised
   // rows to x_res as the next residual.
   for (int l = 0; l < cfg.n_enc; ++l) {
     GemmArgs g = gemm_base(r);

@@ -6,8 +6,8 @@ tolerance (1e-3 float32, 5e-2 bfloat16).
 
 The rows are the ones decoding evaluates: inputs BOS followed by the oracle's
 greedy tokens, plus rows of random tokens (drafts that have not converged), in
-batches of one and of several sentences (the streaming and the tiled product
-kernels)."""
+batches of one and of several sentences (the streaming and the many-row
+vocabulary kernels)."""
 import numpy as np
 import pytest
 
@@ -64,4 +64,4 @@ def test_teacher_forced_logits_mt_shapes(wl):
 
 def test_teacher_forced_logits_large_shape():
     measure("large", 2, 16, 1)
-    measure("large", 2, 16, 2)                     # 32 rows: tiled products
+    measure("large", 2, 16, 2)                     # 32 rows: many-row vocabulary

@@ -24,8 +24,7 @@ MID_F32 = dataclasses.replace(C.TINY, name="mid_f32", d_model=128, n_heads=2, d_
 MID_BF16 = dataclasses.replace(C.TINY, name="mid_bf16", d_model=256, n_heads=8, d_ff=512, vocab=700, dtype=C.BF16)
 WIDE_PRE_BF16 = dataclasses.replace(C.TINY, name="wide_pre", n_dec=1, n_enc=1, d_model=640, n_heads=10, d_ff=640,
                                     vocab=500, pre_ln=True, act_gelu=True, dtype=C.BF16)
-# an FFN down-projection with K = 2048: eight K ranges (split over workgroups
-# in the tiled products of many rows)
+# an FFN down-projection with K = 2048: eight K ranges
 FFN2K_BF16 = dataclasses.replace(C.TINY, name="ffn2k", d_model=256, n_heads=4, d_ff=2048, vocab=700, dtype=C.BF16)
 
 
@@ -175,9 +174,9 @@ def test_rows_are_invariant_to_block_and_batch(cfg):
     g = np.random.default_rng(9)
     tgt = np.concatenate([np.ones((3, 1), np.int32), g.integers(0, cfg.vocab, (3, 89)).astype(np.int32)], 1)
     ctx.encode(torch.from_numpy(np.stack(srcs)).cuda(), [10, 10, 10])
-    full = ctx.debug_logits(torch.from_numpy(tgt)).cpu().numpy()           # 270 rows: separate LN, tiled products
+    full = ctx.debug_logits(torch.from_numpy(tgt)).cpu().numpy()           # 270 rows: separate LN, many-row products
     # 3, 9 and 24 rows: streaming products with the LayerNorm prologue; 90 rows:
-    # the same for d <= 512, separate LN and tiled products for wider models
+    # the same for d <= 512, separate LN and many-row products for wider models
     for T in (1, 3, 8, 30):
         say(f"case row-invariance T={T}")
         part = ctx.debug_logits(torch.from_numpy(np.ascontiguousarray(tgt[:, :T]))).cpu().numpy()
@@ -227,10 +226,10 @@ def test_batch_above_the_inline_length_limit():
                          ids=["tiny_f32", "small_pre_bf16"])
 def test_launch_bound_shrinks_with_the_rows(cfg, wkw):
     """A batch whose rows fall, as sentences finish, from above 128 through 128
-    and 64: its iterations are launched with shrinking bounds (separate
-    LayerNorm and tiled products, then LayerNorm prologues, then the control
-    step that also embeds the next rows), and every sentence still equals its
-    single decode bitwise and the oracle."""
+    and 64: its iterations are launched with shrinking bounds (bfloat16: separate
+    LayerNorm and many-row products first; then LayerNorm prologues, then the
+    control step that also embeds the next rows), and every sentence still
+    equals its single decode bitwise and the oracle."""
     _, _, ctx, M = build(cfg, seed=5, max_batch=4, max_src=16, max_tgt=48, **wkw)
     srcs = sources(cfg.vocab, 4, n=12, seed=11)
     ms = [44, 6, 14, 33]   # Jacobi: 97 rows, then 91, 77 and 44 as sentences finish (k = 6, 14, 33, 37-44)
@@ -292,9 +291,9 @@ def test_degenerate_and_extreme_shapes_match_oracle(cfg):
     """One-token targets and sources, blocks longer than the target, ragged
     batches mixing them with full-length sentences, and the context's maximum
     batch, source and target sizes: every mode against the oracle, and each
-    batched sentence against its own single decode (bf16: the batched
-    iterations of up to 128 rows run on the tiled products and the
-    row-parallel control step)."""
+    batched sentence against its own single decode (the batched iterations
+    of up to 128 rows run on the many-row argmax and the row-parallel control
+    step)."""
     _, _, ctx, M = build(cfg, seed=9, max_batch=4, max_src=32, max_tgt=32, bias_std=0.5, ln_std=0.3)
     g = np.random.default_rng(16)
     modes = [("ar", 1), ("jacobi", 0), ("gs_jacobi", 4), ("gs_jacobi", 40), ("hybrid", 3), ("hybrid", 40)]
@@ -493,7 +492,7 @@ def test_planted_exact_tie_takes_the_lowest_index(cfg, where):
     win (reading R13) -- across workgroup partials (a in another 64-column
     group) and inside one 16-column tile.  a below t must take t's place, a
     above t must never appear.  Checked on the streaming argmax (blocks of <= 16
-    rows), the product / tiled argmax (Jacobi over 32 positions, and 4
+    rows), the many-row argmax (Jacobi over 32 positions, and 4
     sentences x 8) and greedy decoding, against the oracle."""
     w = synth.make_weights(cfg, seed=12, bias_std=0.3, ln_std=0.2)
     M0 = oracle.Model(cfg, w.values)

@@ -94,10 +94,8 @@ def test_trace_matches_oracle_records(cfg, wkw):
                                      (SMALL_PRE_BF16, dict(bias_std=0.3, ln_std=0.2))],
                          ids=["chain_f32", "small_pre_bf16"])
 def test_batched_trace_matches_oracle_per_sentence(cfg, wkw):
-    """Iterations of more than one 16-row tile: the product kernel's argmax
-    epilogue (float) and the tiled kernel's (bf16: up to 64 rows and above 64
-    rows) also return the log-sum-exp partials; each sentence's records equal
-    the oracle's."""
+    """Iterations of more than one 16-row tile: the many-row argmax also returns
+    the log-sum-exp partials; each sentence's records equal the oracle's."""
     gm, ctx, M = build(cfg, seed=7, **wkw)
     srcs = sources(cfg.vocab, 4, seed=24)
     ms = [24, 19, 24, 22]
