@@ -486,7 +486,9 @@ bool few_tiles(int dtype, const GemmArgs& a) {
 // 10.0 / 10.2; V = 20,000, 64 rows [1252] 9.3 / 10.9, 96 rows [1878] 11.9 / 10.6),
 // K = 1024 at 750 (V = 8000, 96 rows 10.3 / 10.0; V = 32,000, 32 rows [1000] 15.2 /
 // 14.9), float32 at 1850 (V = 4003, 384 rows [1512] 12.2 / 14.6, 512 [2016] 15.7 /
-// 14.7; V = 58,101, 32 rows [1816] 24.3 / 26.1, 64 rows [3632] 41.1 / 39.1).
+// 14.7; V = 58,101, 32 rows [1816] 24.3 / 26.1, 64 rows [3632] 41.1 / 39.1), and stored
+// beyond 128 rows (V = 58,101: 48 / 96 / 128 / 256 rows 29.8 / 55.1 / 72.6 / 136, f32x128
+// 39.9 / 64.4 / 73.9 / 134).
 // f32x256 for the bf16 vocabularies that f32x128 would cut into more than 2560
 // (K <= 512) or 6000 units of 16 x 64: V = 58,101, K = 512, 64 stored rows 14.3 / 15.6;
 // K = 1024: V = 80,000, 64 rows [5000] 33.2 / 29.9, V = 250,027, 32 stored 101.7 / 104.0.
@@ -502,10 +504,13 @@ bool few_tiles(int dtype, const GemmArgs& a) {
 // and s128x128 (768 a round) two (V = 32,000, 512 rows [500] 31.8 / 35.1); stored logits
 // from 900 on (V = 250,027, 256 rows 181 / 197; V = 80,000, 384 rows [939] 87 / 93, 256 rows
 // [626] 56 / 47).  s256x256 for stored logits (fuller rows of 256 columns go out
-// together) from 240 on: V = 58,101, K = 512, 512 rows [454] 48, s128x128 61; V = 32,000,
+// together) from 220 on: V = 58,101, K = 512, 512 rows [454] 48, s128x128 61; V = 32,000,
 // 512 rows [250] 35 / 46; V = 8000, 1024 rows [128] 29 / 21.
-// float32, bound by the matrix units: s128x256 for 1536 rows and 480 workgroups on:
-// V = 8000, 2048 rows [512] 131, f32x128 137; V = 58,101, 1024 rows 499 / 470, 2048 919 / 944.
+// float32, bound by the matrix units: a CU takes 63 us per s128x256 tile of K = 512,
+// 71 for as many outputs in f32x128, so s128x256 where at least 0.9 of its outputs on
+// the busiest CU are real: V = 58,101, 1120 rows (0.97) 503 / 548, 1024 rows (0.89) 499 /
+// 470, stored 503 / 501; V = 20,000, 2048 rows (0.98) 310 / 334, 1024 rows (0.81) 190 /
+// 168.  Not with K <= 256, where its epilogue weighs more (V = 4003, K = 256, 2048 rows 51 / 43).
 struct VocabTile {
   int cfg;   // staged, or S_NONE: k_gemm_feed
   int bn;    // columns of a workgroup
@@ -517,10 +522,11 @@ VocabTile vocab_tile(int dtype, int epi, int V, int K, int rows) {
   };
   const bool store = epi == EPI_LOGITS, wide = K > 512;
   if (dtype == DT_F32) {
-    if (rows >= 1536 && wgs(128, 256) >= 480) return {S_128x256, 256};
-    return {S_NONE, wgs(16, 64) <= 1850 ? 64 : 128};
+    const long long big = wgs(128, 256), full = (big + 255) / 256 * 256;
+    if (K > 256 && big >= 240 && 10LL * rows * V >= 9 * full * (128 * 256)) return {S_128x256, 256};
+    return {S_NONE, wgs(16, 64) <= 1850 || (store && rows <= 128) ? 64 : 128};
   }
-  if (store && rows > 448 && wgs(256, 256) >= 240) return {S_256x256, 256};
+  if (store && rows > 448 && wgs(256, 256) >= 220) return {S_256x256, 256};
   if (wide) {
     const long long big = wgs(128, 256);
     if (store ? rows > 128 && big >= 900 : rows > 256 && (big >= 1600 || (big <= 512 && wgs(128, 128) > 768)))

@@ -169,7 +169,7 @@ def test_vocabulary_rows_are_bitwise_those_of_few_rows(dtype, d, heads, vocab, B
 
 @pytest.mark.parametrize("dtype,d,heads,vocab,B,T", [
     ("f32", 64, 4, 1000, 1, 33), ("f32", 64, 4, 1000, 7, 33),            # LayerNorm in the product; 16 x 64 tiles
-    ("f32", 96, 6, 20011, 4, 28), ("f32", 96, 6, 20011, 24, 65),         # 32 x 128; staged 128 x 256
+    ("f32", 96, 6, 20011, 5, 30), ("f32", 288, 18, 20011, 34, 60),       # 32 x 128; staged 128 x 256
     ("bf16", 96, 6, 20011, 2, 40), ("bf16", 96, 6, 58001, 2, 32),        # 32 x 128; 32 x 256
     ("bf16", 96, 6, 20011, 10, 30), ("bf16", 96, 6, 20011, 10, 80),      # staged 128 x 128; 256 x 256
     ("bf16", 640, 10, 20011, 3, 16), ("bf16", 640, 10, 20011, 5, 26),    # 32 x 128; staged 128 x 128
@@ -180,7 +180,7 @@ def test_each_vocabulary_tile_gives_the_rows_of_few_rows(dtype, d, heads, vocab,
 
 
 @pytest.mark.parametrize("dtype,d,heads,vocab,B,m", [
-    ("f32", 128, 2, 20011, 9, 28), ("f32", 128, 2, 20011, 26, 60),       # 32 x 128; staged 128 x 256
+    ("f32", 128, 2, 20011, 9, 28), ("f32", 288, 18, 20011, 34, 60),      # 32 x 128; staged 128 x 256
     ("bf16", 128, 2, 20011, 5, 13), ("bf16", 128, 2, 20011, 9, 16),      # 32 x 128; 32 x 256
     ("bf16", 128, 2, 20011, 9, 28), ("bf16", 640, 10, 20011, 9, 60),     # staged 128 x 128; 128 x 256
     ("bf16", 544, 17, 131200, 3, 13)])                                   # staged 64 x 256
