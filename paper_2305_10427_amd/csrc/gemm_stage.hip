@@ -464,13 +464,14 @@ bool stage_product(int dtype, const GemmArgs& a) {
   return tiles >= (a.K >= 2048 ? 192 : 360);
 }
 
-// Whether a float32 product gives k_gemm_feed too few 32 x 32 tiles for the 256
-// CUs; k_gemm, with a workgroup per 16 x 16, is the faster one then.  us per
+// Whether a narrow float32 product gives k_gemm_feed too few 32 x 32 tiles for the
+// 256 CUs; k_gemm, with a workgroup per 16 x 16, is the faster one then.  us per
 // iteration of three layers, k_gemm_feed / k_gemm below 96 tiles: d = 256, 224
 // rows 173 / 159, 256 rows 164 / 152, 320 rows 172 / 162; d = 128, 256 rows 141 / 134,
 // 448 rows 152 / 146, 576 rows 146 / 146, 768 rows (96 tiles in k_gemm too) 152 / 156.
+// N = 512 with as few (160 rows of d = 512, six encoder layers): 304 / 315.
 bool few_tiles(int dtype, const GemmArgs& a) {
-  return dtype == DT_F32 && a.n_layers <= 1 &&
+  return dtype == DT_F32 && a.n_layers <= 1 && a.N <= 256 &&
          static_cast<long long>((a.n_rows + 31) / 32) * ((a.N + 31) / 32) < 96;
 }
 
