@@ -71,7 +71,8 @@ __global__ __launch_bounds__(64 * KW * WM * WN) void k_gemm_feed(GemmArgs a, int
   const int lr = lane & 15, lg = lane >> 4;
 
   // XCD-aware tile order (see the header comment)
-  const int L = blockIdx.x;
+  constexpr bool VOCAB = EPI == EPI_ARGMAX || EPI == EPI_LOGITS;
+  const int L = VOCAB ? min(static_cast<int>(blockIdx.x + (blockIdx.z << kTilesXBits)), n_tiles - 1) : blockIdx.x;
   const int xcd = L & 7, q8 = n_tiles >> 3, rem = n_tiles & 7;
   const int tile = xcd * q8 + min(xcd, rem) + (L >> 3);
   const int cb = tile / n_rb, rb = tile - cb * n_rb;
@@ -263,14 +264,16 @@ hipError_t launch_shape(const GemmArgs& a, hipStream_t s, bool init) {
   constexpr size_t lds = KW > 1 ? static_cast<size_t>(KW) * BM * (BN + kPartPad) * sizeof(float) : 0;
   const int n_rb = (a.n_rows + BM - 1) / BM;
   const int n_tiles = n_rb * ((a.N + BN - 1) / BN);
-  const int gy = EPI == EPI_QKV && a.n_layers > 1 ? a.n_layers : 1;
+  const dim3 grid = EPI == EPI_ARGMAX || EPI == EPI_LOGITS
+                        ? vocab_tile_grid(n_tiles)
+                        : dim3(n_tiles, EPI == EPI_QKV && a.n_layers > 1 ? a.n_layers : 1);
   auto kernel = &k_gemm_feed<WT, EPI, FM, FN, KW, WM, WN, D>;
   if (init) {          // gfx950 has 160 KB of LDS per CU
     if (lds <= 65536) return hipSuccess;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                static_cast<int>(lds));
   }
-  hipLaunchKernelGGL(kernel, dim3(n_tiles, gy), dim3(64 * KW * WM * WN), lds, s, a, n_rb, n_tiles);
+  hipLaunchKernelGGL(kernel, grid, dim3(64 * KW * WM * WN), lds, s, a, n_rb, n_tiles);
   return hipGetLastError();
 }
 

@@ -10,6 +10,16 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
+// Tiles of a many-row vocabulary launch: the grid's x holds 2^22 at most (2^32
+// threads are more than a dispatch takes), further ones go on in z; workgroups
+// past the last tile repeat it (the same values to the same places; leaving
+// early instead cost the kernels 2%).
+constexpr int kTilesXBits = 22;
+inline dim3 vocab_tile_grid(int n_tiles) {
+  constexpr int x = 1 << kTilesXBits;
+  return n_tiles <= x ? dim3(n_tiles) : dim3(x, 1, (n_tiles - 1) / x + 1);
+}
+
 template <typename T> struct Mma;
 template <> struct Mma<bf16_t> {
   static constexpr int KS = 32;

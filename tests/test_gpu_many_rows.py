@@ -110,6 +110,22 @@ def test_more_sentences_than_a_grid_dimension_holds():
             np.testing.assert_array_equal(x[b], y.cpu().numpy()[0])
 
 
+def test_more_vocabulary_tiles_than_a_grid_dimension_holds():
+    """296,000 rows of V = 58,101: 4.2 million 32 x 128 tiles, more than the 2^22 of the grid's first dimension."""
+    import torch
+    cfg = dataclasses.replace(cfg_of("f32", 32, 1, 32, vocab=58101), n_dec=1)
+    gm = pdec.Model(cfg, synth.make_weights(cfg, seed=8, bias_std=0.1, ln_std=0.1))
+    B, n, m = 18500, 3, 16
+    src = np.random.default_rng(1).integers(4, cfg.vocab, (B, n)).astype(np.int32)
+    ctx, one = pdec.Context(gm, B, n, m), pdec.Context(gm, 1, n, m)
+    ctx.encode(torch.from_numpy(src).cuda(), [n] * B)
+    out = [t.cpu().numpy() for t in ctx.decode("jacobi", [m] * B, max_iters=2)]
+    for b in list(range(0, B, 1999)) + [B - 1]:
+        one.encode(torch.from_numpy(src[b:b + 1]).cuda(), [n])
+        for x, y in zip(out, one.decode("jacobi", [m], max_iters=2)):
+            np.testing.assert_array_equal(x[b], y.cpu().numpy()[0])
+
+
 def launch_bound(rows, full):
     """Rows an iteration of `rows` rows is launched (and its graph captured) for."""
     b = 1
